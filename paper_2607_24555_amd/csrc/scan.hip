@@ -885,7 +885,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   constexpr int G = 16;
   __shared__ __align__(16) uint8_t sTail[4][16][Gm::kTail];
   __shared__ float2 sRun[4][64];
-  __shared__ __align__(16) float sVsc[4][16][R];   // basis column scales x the query scale
+  __shared__ __align__(16) float sVsc[4][16][R];   // basis column scales
   __shared__ __align__(16) float sCsc[4][16][16];  // coefficient row scales
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -956,12 +956,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   #pragma unroll
           for (int u = 0; u < Gm::kTailLoads; ++u) tl[u] = bld16(rs, nx.tl[u]);
         }
-        // the step's scales in fp32, once for its four quads: basis column scales
-        // times the query scale, coefficient row scales
+        // the step's scales in fp32, once for its four quads: basis column scales,
+        // coefficient row scales (the query scale is the reading lane's own: heads
+        // of one group may differ in it)
   #pragma unroll
         for (int u = 0; u < 2; ++u) {
           const int e = lane + 64 * u, pgi = e >> 3, l = e & 7;
-          sVsc[wave][pgi][l] = lds_f16(&sTail[wave][pgi][Gm::kSc + 2 * l]) * QD.inv_scale;
+          sVsc[wave][pgi][l] = lds_f16(&sTail[wave][pgi][Gm::kSc + 2 * l]);
         }
   #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -1025,7 +1026,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   #pragma unroll
               for (int j = 0; j < 4; ++j) {
                 const int sp = 4 * Q + 2 * i + j / 2, pv = sp / V, l = 4 * (j % 2) + grp;
-                vals[4 * i + j] = (float)pacc[pv / 2 - 2 * m][2 * (pv % 2) + j % 2] * sVsc[wave][sp][l];
+                vals[4 * i + j] =
+                    (float)pacc[pv / 2 - 2 * m][2 * (pv % 2) + j % 2] * (sVsc[wave][sp][l] * QD.inv_scale);
               }
           }
           // ---- stage 2 for the quad, then the page LSE in registers

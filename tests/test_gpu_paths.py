@@ -102,6 +102,29 @@ def test_generic_scan_every_rank(rank, q):
     print(f"[paths generic] r={rank} q={q}: max |hat s err| {worst:.2e}")
 
 
+@pytest.mark.parametrize("G,rank,page", [(16, 8, 16), (16, 8, 32), (16, 8, 64), (8, 8, 16),
+                                         (4, 8, 16), (4, 8, 64), (16, 4, 16), (4, 2, 16)])
+def test_scores_of_heads_with_different_query_ranges(G, rank, page):
+    """Heads of one group whose largest query elements lie in different powers of two:
+    each head's scores keep that head's own query scale."""
+    spec = WorkloadSpec("ranges", 1, 2 * G, 2, [page * 150 + 3], rank, 256, "bf16", "bf16",
+                        page_size=page)
+    d = Dev(build_workload(spec, 5))
+    f = torch.tensor([1.0, 0.3, 1.7, 0.07, 0.9, 0.51, 1.2, 0.013])
+    q = d.w.q.float() * f.repeat(2 * G // 8 + 1)[:2 * G, None]
+    d.w.q = q.to(torch.bfloat16)
+    d.q = d.w.q.cuda()
+    store, recs = d.oracle_summaries()
+    out = B.score_pages(d.cfg, d.q, store, d.pt, d.sl, d.ws)
+    torch.cuda.synchronize()
+    for (s, h), rec in recs.items():
+        k, v, qg = d.unit(s, h)
+        ref = O.decode_step(qg, k, v, rec, rank, 256, "int4", page)["s_hat"]
+        n_c = k.shape[0] // page
+        got = out[s, h * G:(h + 1) * G, :n_c].double().cpu().numpy()
+        np.testing.assert_allclose(got, ref[:, :n_c], atol=LSE_TOL, rtol=0)
+
+
 STEP_CASES = {
     # name: (G, rank, kv dtype, q dtype)
     "G16-r2": (16, 2, "bf16", "bf16"),
