@@ -111,7 +111,8 @@ WORKLOADS = {
 # and the same with WRITE_SIZE (KiB per dispatch; per-workload files under profiles/).
 # Each counter is divided by what it reads for the 1 GiB copy over 1 GiB, so the
 # result is in bytes.  Valid only for the scan sources these hashes name.
-SCAN_SOURCES = ("paper_2607_24555_amd/csrc/scan.hip", "paper_2607_24555_amd/csrc/locks_internal.h")
+SCAN_SOURCES = tuple("paper_2607_24555_amd/csrc/" + f for f in (
+    "scan.hip", "scan_quad.h", "scan_wide.h", "scan_low.hip", "scan_common.h", "locks_internal.h"))
 SCAN_TRAFFIC = {
     # workload: (sha256 of SCAN_SOURCES, FETCH_SIZE KiB, WRITE_SIZE KiB,
     #            copy FETCH factor, copy WRITE factor, profile file)

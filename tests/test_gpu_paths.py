@@ -125,6 +125,59 @@ def test_scores_of_heads_with_different_query_ranges(G, rank, page):
         np.testing.assert_allclose(got, ref[:, :n_c], atol=LSE_TOL, rtol=0)
 
 
+def _rank8_against_oracle(d, page, units, rtol=0.0):
+    """Page scores and selected tables of rank-8 units against the oracle."""
+    cfg, G = d.cfg, d.cfg.group
+    store, recs = d.oracle_summaries(units)
+    lse = torch.full((cfg.num_seqs, cfg.num_q_heads, cfg.max_pages_per_seq), float("nan"),
+                     device=d.device)
+    ids, _ = B.select(cfg, d.q, store, d.pt, d.sl, d.ws, out_all_lse=lse)
+    torch.cuda.synchronize()
+    for (s, h), rec in recs.items():
+        k, v, qg = d.unit(s, h)
+        ref = O.decode_step(qg, k, v, rec, 8, cfg.budget_tokens, "int4", page)
+        n_c, n = k.shape[0] // page, -(-k.shape[0] // page)
+        got = lse[s, h * G:(h + 1) * G].double().cpu().numpy()
+        np.testing.assert_allclose(got[:, :n_c], ref["s_hat"][:, :n_c], atol=LSE_TOL, rtol=rtol)
+        assert np.isnan(got[:, n_c:]).all()
+        if not rtol:
+            check_table(ids_of(ids[s, h].tolist()), ref, n, cfg.k)
+
+
+@pytest.mark.parametrize("steps", [1, 4])
+@pytest.mark.parametrize("G,page,q", [(1, 16, "fp32"), (3, 16, "bf16"), (4, 32, "bf16"),
+                                      (5, 32, "bf16"), (7, 16, "bf16"), (8, 16, "fp32"),
+                                      (8, 32, "bf16"), (6, 64, "bf16"), (9, 64, "bf16"),
+                                      (12, 16, "bf16"), (16, 16, "fp32"), (16, 32, "bf16")])
+def test_rank8_scan_groups_and_tile_edges(G, page, q, steps):
+    """The rank-8 scans at every head-column width, page size and query type, with
+    sequences that end on and around the edges of 16-page steps and of a wave's pages,
+    in grids small enough for one step per wave and large enough for four."""
+    edges = [page * n + e for n, e in ((1, 0), (15, 3), (16, 0), (17, 1), (63, 0), (64, 5),
+                                       (65, 0), (130, 2), (0, 5))]
+    if steps == 1:
+        S, Hkv, lens = len(edges), 2, edges
+    else:      # 260 blocks of 256 (sub-)pages: four steps per wave
+        S, Hkv = 65, 4
+        lens = (edges * 8)[:S]
+    spec = WorkloadSpec("groups", S, G * Hkv, Hkv, lens, 8, page * 10, "bf16", q, page_size=page)
+    d = Dev(build_workload(spec, 17))
+    _rank8_against_oracle(d, page, {(s, h) for s in range(len(edges)) for h in (0, Hkv - 1)})
+
+
+@pytest.mark.parametrize("G,page", [(4, 16), (7, 64), (8, 16), (16, 16), (16, 32)])
+def test_rank8_scan_of_widely_spread_logits(G, page):
+    """Pages whose logits spread over more than the range of a float32 exponential:
+    the scan's sums are then taken with the max shifted out (scores of several
+    hundred nats, so float32 rounding enters relative to them)."""
+    spec = WorkloadSpec("spread", 2, 2 * G, 2, [page * 70 + 1, page * 5], 8, page * 10, "bf16",
+                        "bf16", page_size=page)
+    d = Dev(build_workload(spec, 19))
+    d.w.q = (d.w.q.float() * 60).to(torch.bfloat16)
+    d.q = d.w.q.cuda()
+    _rank8_against_oracle(d, page, {(s, h) for s in (0, 1) for h in (0, 1)}, rtol=2e-6)
+
+
 STEP_CASES = {
     # name: (G, rank, kv dtype, q dtype)
     "G16-r2": (16, 2, "bf16", "bf16"),
