@@ -1,20 +1,28 @@
 // Per-page summary construction for pages of B = 32 or 64 tokens (Sec. 4
 // "Build"; App. D.3 "Page size"): centre the page's B keys, form the B x B Gram of
 // the deviations, find its eigenpairs, keep the r leading nonzero modes, form
-// V = D^T U_r S_r^{-1} and C = U_r S_r, quantise and pack.
+// V = D^T U_r S_r^{-1} and C = U_r S_r, quantise and pack.  Everything is fp32.
 //
-// The symmetric eigenproblem is solved with B lanes, one row each: Householder
-// reduction to a tridiagonal T (the rows in LDS; the reflector and its update
-// vectors broadcast through LDS), the wanted eigenvalues of T by multisection on
-// Sturm counts (B / n lanes per eigenvalue), the r leading eigenvectors of T by
-// inverse iteration on its LDL^T factorisation (lane l solves for vector l; two
-// rounds, each followed by modified Gram-Schmidt over the r vectors, so a
-// near-degenerate pair still yields an orthonormal basis of its eigenspace), and
-// the back-transformation through the stored reflectors.  Everything is fp32.
-// Cross-lane sums use DPP within 16-lane rows and row swaps across them.
-//
-// Mapping: one wave per block holding 64 / B items (page, KV head); lane (it, i)
-// owns row i of item it.
+// Mapping: one wave per block holding kI = 64 / B items (page, KV head).
+//  * Centroid, Gram (upper 16 x 16 tiles) and V take their key operands straight from
+//    memory in the layout their lanes need and run on all 64 lanes, item by item; the
+//    Gram and V are fp32 MFMAs 16x16x4.
+//  * Eigenproblem: lane (it, i) holds row i of item it's Gram in registers.  Householder
+//    reduction from the last column down (step k annihilates column k above row k - 1):
+//    the reflector and its update vector reach every lane as 16-lane segments copied to
+//    all rows by lane swaps, whose elements are row broadcasts folded into the FMAs, so
+//    a step costs three FMAs per 16-column group and lane and no LDS in its loops (with
+//    the rows in LDS the loops were bound by LDS bandwidth, six 16-byte accesses per
+//    four columns).  The steps are unrolled by 16 inside a loop over the groups: every
+//    register index is static and the code stays well inside the instruction cache.
+//  * The wanted eigenvalues of T by multisection on Sturm counts (B / n lanes per
+//    eigenvalue), the r leading eigenvectors of T by inverse iteration on its LDL^T
+//    factorisation (lane l solves for vector l in registers; two rounds, each followed
+//    by modified Gram-Schmidt over the r vectors, so a near-degenerate pair still
+//    yields an orthonormal basis of its eigenspace).
+//  * Back-transformation with kCPL components of one vector per lane: a reflector is one
+//    short dot product, a few lane exchanges and one update.
+#include "build_common.h"
 #include "locks_internal.h"
 
 namespace locks {
@@ -22,50 +30,55 @@ namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 
-constexpr float kZeroRel = 1e-6f;
-constexpr float kZeroAbs = 1e-10f;
 constexpr int kInvRounds = 2;     // inverse-iteration rounds (solve + orthogonalise)
-
-template <int B>
-struct PG {
-  static constexpr int kItems = 64 / B;       // items per wave
-  static constexpr int kCols = kDim / B;      // key columns per lane (centroid, basis)
-  static constexpr int kPad = B + 4;          // LDS row stride (floats) of the Gram
-  static constexpr int kVec = B + 1;          // LDS stride (floats) of a lane's vector
-  static constexpr int kKeyParts = B == 32 ? 2 : 1;  // column parts of the key rows in LDS
-};
 
 template <int C>
 __device__ __forceinline__ float dpp_f(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), C, 0xF, 0xF, false));
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), C, 0xF, 0xF, true));
 }
-// Sum / max over the B lanes of an item (lane groups of B consecutive lanes):
-// within a 16-lane row by DPP (quad xor 1, quad xor 2, half-row mirror, row
-// mirror), across rows by lane swaps.
-// (a row swap pairs rows 0-1 and 2-3, a half swap the two halves of the wave:
-// the two results summed hold the pair's total in both)
+__device__ __forceinline__ float swap16_add(float v) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+__device__ __forceinline__ float swap32_add(float v) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+// Sums over the B lanes of an item (lane groups of B consecutive lanes) of N values,
+// stage by stage so that the N chains overlap: within a 16-lane row by DPP (quad xor 1,
+// quad xor 2, half-row mirror, row mirror), across rows by lane swaps.
+template <int B, int N>
+__device__ __forceinline__ void group_sums(float (&v)[N]) {
+#pragma unroll
+  for (int n = 0; n < N; ++n) v[n] += dpp_f<0xB1>(v[n]);
+#pragma unroll
+  for (int n = 0; n < N; ++n) v[n] += dpp_f<0x4E>(v[n]);
+#pragma unroll
+  for (int n = 0; n < N; ++n) v[n] += dpp_f<0x141>(v[n]);
+#pragma unroll
+  for (int n = 0; n < N; ++n) v[n] += dpp_f<0x140>(v[n]);
+  if (B >= 32)
+#pragma unroll
+    for (int n = 0; n < N; ++n) v[n] = swap16_add(v[n]);
+  if (B >= 64)
+#pragma unroll
+    for (int n = 0; n < N; ++n) v[n] = swap32_add(v[n]);
+}
 template <int B>
 __device__ __forceinline__ float group_sum(float v) {
-  v += dpp_f<0xB1>(v);
-  v += dpp_f<0x4E>(v);
-  v += dpp_f<0x141>(v);
-  v += dpp_f<0x140>(v);
-  if (B >= 32) {
-    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-  }
-  if (B >= 64) {
-    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-  }
-  return v;
+  float a[1] = {v};
+  group_sums<B, 1>(a);
+  return a[0];
 }
-template <int B>
-__device__ __forceinline__ float group_max(float v) {
+__device__ __forceinline__ float row_max(float v) {
   v = fmaxf(v, dpp_f<0xB1>(v));
   v = fmaxf(v, dpp_f<0x4E>(v));
   v = fmaxf(v, dpp_f<0x141>(v));
-  v = fmaxf(v, dpp_f<0x140>(v));
+  return fmaxf(v, dpp_f<0x140>(v));
+}
+template <int B>
+__device__ __forceinline__ float group_max(float v) {
+  v = row_max(v);
   if (B >= 32) {
     const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     v = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
@@ -76,322 +89,354 @@ __device__ __forceinline__ float group_max(float v) {
   }
   return v;
 }
-template <int B>
-__device__ __forceinline__ int group_min_int(int v) {
+__device__ __forceinline__ int row_min_int(int v) {
   v = min(v, __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false));
   v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false));
   v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, false));
-  v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, false));
-  if (B >= 32) {
-    const auto p = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
-    v = min((int)p[0], (int)p[1]);
-  }
-  if (B >= 64) {
-    const auto p = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
-    v = min((int)p[0], (int)p[1]);
-  }
-  return v;
+  return min(v, __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, false));
 }
 
-// Elements of a 16-byte chunk of bf16 or fp32 keys as floats.
-template <typename KT>
-__device__ __forceinline__ void chunk_to_f(const uint4& w, float* out);
-template <>
-__device__ __forceinline__ void chunk_to_f<uint16_t>(const uint4& w, float* out) {
-  const uint32_t u[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    out[2 * e] = __uint_as_float(u[e] << 16);
-    out[2 * e + 1] = __uint_as_float(u[e] & 0xffff0000u);
+// Item vector x (lane (it, i) holds x_i) as B / 16 segments: lane l of seg[g] holds
+// x_{16 g + l % 16} of its item.
+template <int B>
+__device__ __forceinline__ void segments(float x, float (&seg)[B / 16]) {
+  const uint32_t u = __float_as_uint(x);
+  const auto xy = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  if constexpr (B == 32) {
+    seg[0] = __uint_as_float(xy[0]);
+    seg[1] = __uint_as_float(xy[1]);
+  } else {
+    const auto xx = __builtin_amdgcn_permlane32_swap(xy[0], xy[0], false, false);
+    const auto yy = __builtin_amdgcn_permlane32_swap(xy[1], xy[1], false, false);
+    seg[0] = __uint_as_float(xx[0]);
+    seg[1] = __uint_as_float(yy[0]);
+    seg[2] = __uint_as_float(xx[1]);
+    seg[3] = __uint_as_float(yy[1]);
   }
 }
-template <>
-__device__ __forceinline__ void chunk_to_f<float>(const uint4& w, float* out) {
-  out[0] = __uint_as_float(w.x); out[1] = __uint_as_float(w.y);
-  out[2] = __uint_as_float(w.z); out[3] = __uint_as_float(w.w);
+
+// The FMAs of a Householder step whose first factor is one element of a segment, read by
+// a row broadcast in the FMA itself (the compiler keeps the broadcast as a move of its own,
+// twice the instructions).  Each block opens with the two wait states that a DPP read
+// needs after the write of its source, whatever the compiler placed before it.
+#define LOCKS_BC(J) " row_newbcast:" #J " row_mask:0xf bank_mask:0xf\n"
+// p += sum_j seg_j a_j over eight columns from J0 = 0 or 8 of the segment
+template <int J0>
+__device__ __forceinline__ void dot8(float& p, float seg, const float (&a)[8]) {
+  static_assert(J0 == 0 || J0 == 8, "half of a segment");
+#define LOCKS_D(O, J) "v_fmac_f32_dpp %0, %1, %" #O LOCKS_BC(J)
+  if constexpr (J0 == 0)
+    asm("s_nop 1\n" LOCKS_D(2, 0) LOCKS_D(3, 1) LOCKS_D(4, 2) LOCKS_D(5, 3) LOCKS_D(6, 4)
+            LOCKS_D(7, 5) LOCKS_D(8, 6) LOCKS_D(9, 7)
+        : "+v"(p)
+        : "v"(seg), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]),
+          "v"(a[7]));
+  else
+    asm("s_nop 1\n" LOCKS_D(2, 8) LOCKS_D(3, 9) LOCKS_D(4, 10) LOCKS_D(5, 11) LOCKS_D(6, 12)
+            LOCKS_D(7, 13) LOCKS_D(8, 14) LOCKS_D(9, 15)
+        : "+v"(p)
+        : "v"(seg), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]),
+          "v"(a[7]));
+#undef LOCKS_D
+}
+// a_j += vseg_j nw + wseg_j nv over eight columns from J0 of the segments
+template <int J0>
+__device__ __forceinline__ void rank2_8(float* a, float vseg, float wseg, float nv, float nw) {
+  static_assert(J0 == 0 || J0 == 8, "half of a segment");
+#define LOCKS_U(O, J) "v_fmac_f32_dpp %" #O ", %8, %11" LOCKS_BC(J) "v_fmac_f32_dpp %" #O ", %9, %10" LOCKS_BC(J)
+  if constexpr (J0 == 0)
+    asm("s_nop 1\n" LOCKS_U(0, 0) LOCKS_U(1, 1) LOCKS_U(2, 2) LOCKS_U(3, 3) LOCKS_U(4, 4)
+            LOCKS_U(5, 5) LOCKS_U(6, 6) LOCKS_U(7, 7) "s_nop 1\n"
+        : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]),
+          "+v"(a[7])
+        : "v"(vseg), "v"(wseg), "v"(nv), "v"(nw));
+  else
+    asm("s_nop 1\n" LOCKS_U(0, 8) LOCKS_U(1, 9) LOCKS_U(2, 10) LOCKS_U(3, 11) LOCKS_U(4, 12)
+            LOCKS_U(5, 13) LOCKS_U(6, 14) LOCKS_U(7, 15) "s_nop 1\n"
+        : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]),
+          "+v"(a[7])
+        : "v"(vseg), "v"(wseg), "v"(nv), "v"(nw));
+#undef LOCKS_U
+}
+#undef LOCKS_BC
+
+template <int N>
+struct Int {
+  static constexpr int value = N;
+};
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_range(F&& f) {
+  if constexpr (I < N) {
+    f(Int<I>{});
+    static_range<I + 1, N>(f);
+  }
 }
 
-__device__ __forceinline__ float f16_scale(float amax, float qmax) {
-  float s = fminf(amax / qmax, 65504.0f);
-  return (float)(_Float16)s;
-}
-__device__ __forceinline__ int quant(float x, float s, int qmax) {
-  if (!(s > 0.0f)) return 0;
-  float c = rintf(x / s);
-  c = fminf(fmaxf(c, (float)-qmax), (float)qmax);
-  return (int)c;
-}
-__device__ __forceinline__ uint16_t f16_bits(float s) {
-  _Float16 h = (_Float16)s;
-  return *reinterpret_cast<uint16_t*>(&h);
-}
-__device__ __forceinline__ uint32_t bf16_rne_bits(float f) {
-  const uint32_t u = __float_as_uint(f);
-  return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+// Reflector of column k (rows 0 .. k - 1): 16 (seg + 1) floats, seg = (k - 1) / 16.
+__device__ __forceinline__ int refl_off(int k) {
+  const int seg = (k - 1) >> 4;
+  return 128 * seg * (seg + 1) + 16 * (seg + 1) * ((k - 1) & 15);
 }
 
-template <typename KT>
-__device__ __forceinline__ float key_at(const KT* p, int c) { return load_elem(p, c); }
+// One (page, KV head) of the block; uniform over the wave.
+struct PageItem {
+  bool active;
+  int h, e;
+  long row;  // blk * H_kv + h
+};
 
 template <typename KT, int B, bool kFactors, int kMaxR>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void build_page_kernel(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(B == 32 && kMaxR <= 8 ? 4 : 2))) void build_page_kernel(
     int S, int H_kv, int max_pages, int r, const KT* __restrict__ k_cache,
     const int32_t* __restrict__ page_table, const int32_t* __restrict__ seq_lens,
     const int32_t* __restrict__ build_list, int n_items, int all_pages,
     uint8_t* __restrict__ summaries, float* __restrict__ mu_out, float* __restrict__ basis_out,
-    float* __restrict__ coef_out, float* __restrict__ sigma2_out, int basis) {
-  using P = PG<B>;
-  constexpr int kI = P::kItems;
-  // phase-shared LDS: key rows (load, centroid, Gram), then the Gram rows and the
-  // reflectors, then U, then the packed record; the inverse-iteration arrays
-  // have their own
-  constexpr int kKBytes = kI * B * (kDim / P::kKeyParts) * (int)sizeof(KT);  // one part of the key rows
-  constexpr int kABytes = kI * B * P::kPad * 4;
-  constexpr int kRecBytes = kI * rec_stride(kMaxR, LOCKS_BASIS_BF16, B);
-  constexpr int kBig0 = kKBytes > kABytes ? kKBytes : kABytes;
-  constexpr int kBig = kBig0 > kRecBytes ? kBig0 : kRecBytes;
-  __shared__ __align__(16) uint8_t sBuf[kBig];
-  __shared__ float sInv[3 * kI * kMaxR * P::kVec];  // [3][kI][kMaxR][kVec]: M, W, X
+    float* __restrict__ coef_out, float* __restrict__ sigma2_out) {
+  constexpr int kI = 64 / B;            // items per wave
+  constexpr int kNG = B / 16;           // 16-column groups
+  constexpr int kVec = 16 / (int)sizeof(KT);  // key elements per 16-byte load
+  constexpr int kPad = B + 4;           // LDS row stride (floats) of Gram rows and vectors
+  constexpr int kCPL = kMaxR <= 8 ? 8 : 16;   // vector components per lane (back-transform)
+  constexpr int kLPV = B / kCPL;              // lanes per vector
+  constexpr int kUS = kMaxR <= 8 ? 9 : 17;    // LDS stride (floats) of a row of U
+  // LDS phases of sBig: 32 Gram rows at a time (layout change), the reflectors, U
+  constexpr int kGramF = 32 * kPad, kReflF = kI * 128 * kNG * (kNG + 1), kUF = kI * B * kUS;
+  constexpr int kBig0 = kGramF > kReflF ? kGramF : kReflF;
+  __shared__ __align__(16) float sBig[kBig0 > kUF ? kBig0 : kUF];
+  __shared__ __align__(16) float sX[kI][kMaxR <= 8 ? 8 : 16][kPad];  // eigenvectors of T
   __shared__ __align__(16) float sMu[kI][kDim];
-  __shared__ __align__(16) float sD[kI][B];      // diagonal of T
-  __shared__ __align__(16) float sE[kI][B];      // off-diagonal of T (e[k] couples k, k+1)
-  __shared__ __align__(16) float sE2[kI][B];     // e[k - 1]^2 (0 for k = 0), Sturm counts
+  __shared__ __align__(16) float sD[kI][B];   // diagonal of T
+  __shared__ __align__(16) float sE[kI][B];   // off-diagonal of T (e[k] couples k, k + 1)
+  __shared__ __align__(16) float sE2[kI][B];  // e[k - 1]^2 (Sturm counts)
   __shared__ float sTau[kI][B];
-  __shared__ __align__(16) float sV[kI][B];      // reflector broadcast
-  __shared__ __align__(16) float sW[kI][B];      // update-vector broadcast
-  __shared__ float sLam[kI][B];                  // eigenvalues, descending
-  __shared__ float sFlip[kI][kMaxR];
-  auto& sK = *reinterpret_cast<KT(*)[kI][B][kDim / P::kKeyParts]>(sBuf);
-  auto& sA = *reinterpret_cast<float(*)[kI][B][P::kPad]>(sBuf);
-  auto inv = [&](int which, int it, int l) -> float* {
-    return sInv + ((which * kI + it) * kMaxR + l) * P::kVec;
-  };
+  __shared__ float sLam[kI][B];               // eigenvalues, descending
+  __shared__ float sFlip[kI][16];
 
   const int lane = threadIdx.x;
   const int it = lane / B, i = lane % B;
-  const long item = (long)blockIdx.x * kI + it;
+  const int l16 = lane & 15, q4 = lane >> 4;
 
-  // ---- which (seq, page, KV head) this item builds
-  bool active = false;
-  int s = 0, j = 0, h = 0, e = 0;
-  if (all_pages) {
-    h = (int)(item % H_kv);
-    const long t = item / H_kv;
-    j = (int)(t % max_pages);
-    s = (int)(t / max_pages);
-    active = s < S && j < seq_lens[s] / B;
-  } else {
-    h = (int)(item % H_kv);
-    e = (int)(item / H_kv);
-    if (e < n_items) {
-      s = build_list[2 * e];
-      j = build_list[2 * e + 1];
-      active = s >= 0 && s < S && j >= 0 && j < max_pages && j < seq_lens[s] / B;
+  // ---- which (seq, page, KV head) the block's items are
+  PageItem item[kI];
+  bool any = false;
+#pragma unroll
+  for (int t = 0; t < kI; ++t) {
+    const long id = (long)blockIdx.x * kI + t;
+    PageItem p{false, (int)(id % H_kv), 0, 0};
+    const long rest = id / H_kv;
+    int s = 0, j = 0;
+    if (all_pages) {
+      j = (int)(rest % max_pages);
+      s = (int)(rest / max_pages);
+      p.active = s < S && j < seq_lens[s < S ? s : 0] / B;
+    } else if (rest < n_items) {
+      p.e = (int)rest;
+      s = build_list[2 * rest];
+      j = build_list[2 * rest + 1];
+      p.active = s >= 0 && s < S && j >= 0 && j < max_pages && j < seq_lens[s >= 0 && s < S ? s : 0] / B;
     }
+    const long blk = p.active ? (long)page_table[(long)s * max_pages + j] : 0;
+    p.row = blk * H_kv + p.h;
+    any |= p.active;
+    item[t] = p;
   }
-  if (!__any(active)) return;
-  const long blk = active ? (long)page_table[(long)s * max_pages + j] : 0;
-  const KT* kpage = k_cache + (blk * H_kv + h) * (long)B * kDim;
+  if (!any) return;
+  auto kpage = [&](int t) { return k_cache + item[t].row * (long)B * kDim; };
+  // 16 bytes of token `tok` of item t from element c (zeros for an inactive item)
+  auto key16 = [&](int t, int tok, int c) {
+    return item[t].active ? *reinterpret_cast<const uint4*>(kpage(t) + tok * kDim + c)
+                          : make_uint4(0, 0, 0, 0);
+  };
 
-  // ---- key rows, centroid and Gram in kParts column parts: the LDS holds one
-  //      part of the item's key rows at a time (the squared norm of row i
-  //      accumulates from the registers).  32-token pages take two parts, so the
-  //      key rows need no more LDS than the Gram rows; at 64 tokens the Gram rows
-  //      need more than all the key rows, and one part keeps the registers down.
-  constexpr int kParts = P::kKeyParts;
-  constexpr int kHalf = kDim / kParts;
-  constexpr int kV = 16 / sizeof(KT);
-  constexpr int kT = B / 16;
-  constexpr int kTiles = kT * (kT + 1) / 2;
+  // ---- centroid and mean squared norm: lane (q4, l16) sums dims 8 l16 .. + 7 over the
+  //      tokens 4 s + q4, pairwise (exact for equal rows), then over q4
   float energy = 0.0f;
-  f4 acc[kI][kTiles];
 #pragma unroll
-  for (int t = 0; t < kI; ++t)
+  for (int t = 0; t < kI; ++t) {
+    float en = 0.0f, sum[8];
+    // partial sums over runs of s, merged as a binary counter
+    float part[5][8];
 #pragma unroll
-    for (int tile = 0; tile < kTiles; ++tile) acc[t][tile] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int s = 0; s < B / 4; ++s) {
+      float x[8];
 #pragma unroll
-  for (int hf = 0; hf < kParts; ++hf) {
-    {
-      const uint4* src = reinterpret_cast<const uint4*>(kpage + (long)i * kDim + hf * kHalf);
-      uint4 w[kHalf / kV];
+      for (int u = 0; u < 8 / kVec; ++u)
+        chunk_to_f<KT>(key16(t, 4 * s + q4, 8 * l16 + u * kVec), &x[u * kVec]);
 #pragma unroll
-      for (int u = 0; u < kHalf / kV; ++u) w[u] = active ? src[u] : make_uint4(0, 0, 0, 0);
-      uint4* dst = reinterpret_cast<uint4*>(&sK[it][i][0]);
+      for (int e = 0; e < 8; ++e) en = fmaf(x[e], x[e], en);
+      int lvl = 0;
 #pragma unroll
-      for (int u = 0; u < kHalf / kV; ++u) dst[u] = w[u];
+      for (int b = 0; b < 4; ++b)
+        if (((s >> b) & 1) && lvl == b) {
 #pragma unroll
-      for (int u = 0; u < kHalf / kV; ++u) {
-        float x[kV];
-        chunk_to_f<KT>(w[u], x);
-#pragma unroll
-        for (int e2 = 0; e2 < kV; ++e2) energy = fmaf(x[e2], x[e2], energy);
-      }
-      __syncthreads();
-    }
-    // centroid of the lane's kHC columns of the part: pairwise sum over the B rows
-    // (exact when the rows are equal)
-    {
-      constexpr int kHC = kHalf / B;
-      float v[B][kHC];
-#pragma unroll
-      for (int t = 0; t < B; ++t)
-#pragma unroll
-        for (int cc = 0; cc < kHC; ++cc) v[t][cc] = key_at(&sK[it][t][0], kHC * i + cc);
-#pragma unroll
-      for (int w = B / 2; w > 0; w >>= 1)
-#pragma unroll
-        for (int t = 0; t < w; ++t)
-#pragma unroll
-          for (int cc = 0; cc < kHC; ++cc) v[t][cc] = v[t][cc] + v[t + w][cc];
-#pragma unroll
-      for (int cc = 0; cc < kHC; ++cc) sMu[it][hf * kHalf + kHC * i + cc] = v[0][cc] * (1.0f / B);
-    }
-    __syncthreads();
-    // Gram of the deviations on fp32 MFMA 16x16x4, one 16 x 16 tile at a time:
-    // lane l supplies row 16 T + l % 16 (A) and 16 U + l % 16 (B) at columns
-    // kGC (l / 16) + m, m < kGC, of the part; register jj then holds
-    // G[16 T + 4 (l/16) + jj][16 U + l % 16].  Upper tiles only; the lower
-    // triangle is mirrored.
-    constexpr int kGC = kHalf / 4;
-    {
-      const int l16 = lane & 15, q4 = lane >> 4;
-#pragma unroll
-      for (int t = 0; t < kI; ++t) {
-        int tile = 0;
-#pragma unroll
-        for (int T = 0; T < kT; ++T)
-#pragma unroll
-          for (int U = T; U < kT; ++U) {
-            f4 a = acc[t][tile];
-#pragma unroll
-            for (int ch = 0; ch < kGC / kV; ++ch) {
-              const int c0 = kGC * q4 + kV * ch;
-              const uint4 wx = *reinterpret_cast<const uint4*>(&sK[t][16 * T + l16][c0]);
-              const uint4 wy = *reinterpret_cast<const uint4*>(&sK[t][16 * U + l16][c0]);
-              float xs[kV], ys[kV];
-              chunk_to_f<KT>(wx, xs);
-              chunk_to_f<KT>(wy, ys);
-#pragma unroll
-              for (int e2 = 0; e2 < kV; ++e2) {
-                const float m2 = sMu[t][hf * kHalf + c0 + e2];
-                a = __builtin_amdgcn_mfma_f32_16x16x4f32(xs[e2] - m2, ys[e2] - m2, a, 0, 0, 0);
-              }
-            }
-            acc[t][tile++] = a;
-          }
-      }
-    }
-    __syncthreads();  // the next part (or the Gram rows) takes the key rows' LDS
-  }
-  energy = group_sum<B>(energy) * (1.0f / B);
-  {
-    const int l16 = lane & 15, q4 = lane >> 4;
-#pragma unroll
-    for (int t = 0; t < kI; ++t) {
-      int tile = 0;
-#pragma unroll
-      for (int T = 0; T < kT; ++T)
-#pragma unroll
-        for (int U = T; U < kT; ++U) {
-#pragma unroll
-          for (int jj = 0; jj < 4; ++jj) {
-            const int row = 16 * T + 4 * q4 + jj, col = 16 * U + l16;
-            if (row <= col) {
-              sA[t][row][col] = acc[t][tile][jj];
-              sA[t][col][row] = acc[t][tile][jj];
-            }
-          }
-          ++tile;
+          for (int e = 0; e < 8; ++e) x[e] = part[b][e] + x[e];
+          lvl = b + 1;
         }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) part[lvl][e] = x[e];
     }
+    constexpr int kTop = B == 64 ? 4 : 3;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sum[e] = swap16_add(swap32_add(part[kTop][e])) * (1.0f / B);
+    if (q4 == 0) {
+      *reinterpret_cast<float4*>(&sMu[t][8 * l16]) = make_float4(sum[0], sum[1], sum[2], sum[3]);
+      *reinterpret_cast<float4*>(&sMu[t][8 * l16 + 4]) = make_float4(sum[4], sum[5], sum[6], sum[7]);
+    }
+    en = group_sum<64>(en) * (1.0f / B);
+    energy = it == t ? en : energy;
   }
   __syncthreads();
 
-  // ---- Householder reduction to tridiagonal form, rows in LDS.  Step k
-  //      annihilates column k below the subdiagonal with H = I - tau v v^T (v[k+1]
-  //      = 1) and updates the trailing block by the rank-2 form A - v w^T - w v^T;
-  //      v is then kept in column k of the rows below k + 1 for the
-  //      back-transformation.  Entries of v, p and w at indices <= k are zero, so
-  //      every lane runs the same row loops over the 4-column groups from the one
-  //      holding column k + 1 on (the skipped products are exact zeros).
-  float* arow = &sA[it][i][0];
-  for (int k = 0; k < B - 2; ++k) {
-    const float x = arow[k];
-    const float sig = group_sum<B>(i > k + 1 ? x * x : 0.0f);
-    const float x0 = group_sum<B>(i == k + 1 ? x : 0.0f);
-    float tau = 0.0f, v0 = 1.0f, beta = x0;
-    if (sig > 0.0f) {
-      const float mu = sqrtf(fmaf(x0, x0, sig));
-      v0 = x0 <= 0.0f ? x0 - mu : -sig / (x0 + mu);
-      tau = 2.0f * v0 * v0 / (sig + v0 * v0);
-      beta = mu;
+  // ---- Gram of the deviations on fp32 MFMA 16x16x4, upper tiles: the lane supplies rows
+  //      16 T + l16 at columns kVec (4 ch + q4) + m as both operands; register jj then
+  //      holds G[16 T + 4 q4 + jj][16 U + l16].  Row i goes to lane i through LDS, 32
+  //      rows of an item at a time.
+  float a[B];
+  {
+    constexpr int kTiles = kNG * (kNG + 1) / 2;
+    f4 acc[kI][kTiles];
+#pragma unroll
+    for (int t = 0; t < kI; ++t) {
+#pragma unroll
+      for (int n = 0; n < kTiles; ++n) acc[t][n] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int ch = 0; ch < kDim / (4 * kVec); ++ch) {
+        const int c0 = kVec * (4 * ch + q4);
+        float x[kNG][kVec];
+#pragma unroll
+        for (int T = 0; T < kNG; ++T) chunk_to_f<KT>(key16(t, 16 * T + l16, c0), x[T]);
+#pragma unroll
+        for (int m = 0; m < kVec; ++m) {
+          const float mu = sMu[t][c0 + m];
+#pragma unroll
+          for (int T = 0; T < kNG; ++T) x[T][m] -= mu;
+          int n = 0;
+#pragma unroll
+          for (int T = 0; T < kNG; ++T)
+#pragma unroll
+            for (int U = T; U < kNG; ++U) {
+              acc[t][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[T][m], x[U][m], acc[t][n], 0, 0, 0);
+              ++n;
+            }
+        }
+      }
     }
-    const float vi = i == k + 1 ? 1.0f : (i > k + 1 && sig > 0.0f ? x / v0 : 0.0f);
-    if (i == k) {
-      sD[it][k] = x;
-      sE[it][k] = beta;
-      sTau[it][k] = tau;
+    // 32 rows at a time: item st (B = 32) or rows 32 st .. of the item (B = 64)
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+      const int t = B == 32 ? st : 0, hf = B == 32 ? 0 : st;
+      float* A = sBig - hf * 32 * kPad;
+      int n = 0;
+#pragma unroll
+      for (int T = 0; T < kNG; ++T)
+#pragma unroll
+        for (int U = T; U < kNG; ++U) {
+          const f4 g = acc[t][n++];
+          if (U / 2 == hf)  // G[16 U + l16][16 T + 4 q4 + jj], by symmetry
+            *reinterpret_cast<float4*>(A + (16 * U + l16) * kPad + 16 * T + 4 * q4) =
+                make_float4(g[0], g[1], g[2], g[3]);
+          if (U != T && T / 2 == hf)
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) A[(16 * T + 4 * q4 + jj) * kPad + 16 * U + l16] = g[jj];
+        }
+      __syncthreads();
+      const bool mine = (lane >> 5) == st;
+      const float* row = sBig + (lane & 31) * kPad;
+#pragma unroll
+      for (int q = 0; q < B / 4; ++q) {
+        const float4 v = *reinterpret_cast<const float4*>(row + 4 * q);
+        if (st == 0 || mine) {
+          a[4 * q] = v.x;
+          a[4 * q + 1] = v.y;
+          a[4 * q + 2] = v.z;
+          a[4 * q + 3] = v.w;
+        }
+      }
+      __syncthreads();
     }
-    sV[it][i] = vi;
-    __builtin_amdgcn_wave_barrier();
-    // p = tau A v over the trailing block
-    const int q0 = (k + 1) >> 2;
-    float p = 0.0f;
-#pragma unroll 4
-    for (int q = q0; q < B / 4; ++q) {
-      const float4 r4 = *reinterpret_cast<const float4*>(arow + 4 * q);
-      const float4 v4 = *reinterpret_cast<const float4*>(&sV[it][4 * q]);
-      p = fmaf(r4.x, v4.x, p);
-      p = fmaf(r4.y, v4.y, p);
-      p = fmaf(r4.z, v4.z, p);
-      p = fmaf(r4.w, v4.w, p);
-    }
-    p = i > k ? tau * p : 0.0f;
-    const float kc = 0.5f * tau * group_sum<B>(p * vi);
-    const float wi = p - kc * vi;
-    sW[it][i] = wi;
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll 4
-    for (int q = q0; q < B / 4; ++q) {
-      float4 r4 = *reinterpret_cast<const float4*>(arow + 4 * q);
-      const float4 v4 = *reinterpret_cast<const float4*>(&sV[it][4 * q]);
-      const float4 w4 = *reinterpret_cast<const float4*>(&sW[it][4 * q]);
-      r4.x = fmaf(-vi, w4.x, fmaf(-wi, v4.x, r4.x));
-      r4.y = fmaf(-vi, w4.y, fmaf(-wi, v4.y, r4.y));
-      r4.z = fmaf(-vi, w4.z, fmaf(-wi, v4.z, r4.z));
-      r4.w = fmaf(-vi, w4.w, fmaf(-wi, v4.w, r4.w));
-      *reinterpret_cast<float4*>(arow + 4 * q) = r4;
-    }
-    __builtin_amdgcn_wave_barrier();
-    if (i > k + 1) arow[k] = vi;  // reflector component, for the back-transformation
-    __builtin_amdgcn_wave_barrier();
   }
-  if (i == B - 2) {
-    sD[it][B - 2] = arow[B - 2];
-    sE[it][B - 2] = arow[B - 1];
+
+  // ---- Householder reduction to tridiagonal form.  Step k annihilates column k above
+  //      row k - 1 with H = I - tau v v^T (v_{k-1} = 1) and updates the leading block by
+  //      the rank-2 form A - v w^T - w v^T.  v and w are zero at rows >= k, so whole
+  //      16-column groups run without a mask (the skipped products are exact zeros).
+  float* refl = sBig + it * 128 * kNG * (kNG + 1);
+#pragma unroll 1
+  for (int t = kNG - 1; t >= 0; --t) {
+    static_range<0, 16>([&](auto sc) __attribute__((always_inline)) {
+      constexpr int s = 15 - decltype(sc)::value;
+      const int k = 16 * t + s;
+      if (s < 2 && t == 0) return;  // columns 1 and 0 are done
+      const int tg = s == 0 ? t - 1 : t;  // group of row k - 1
+      float x = a[s];
+#pragma unroll
+      for (int g = 1; g < kNG; ++g) x = t == g ? a[16 * g + s] : x;
+      float x0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), k - 1));
+      if (kI == 2) {
+        const float x1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), B + k - 1));
+        x0 = it ? x1 : x0;
+      }
+      const float sig = group_sum<B>(i < k - 1 ? x * x : 0.0f);
+      float tau = 0.0f, v0 = 1.0f, beta = x0;
+      if (sig > 0.0f) {
+        const float mu = __builtin_amdgcn_sqrtf(fmaf(x0, x0, sig));
+        v0 = x0 <= 0.0f ? x0 - mu : -sig * __builtin_amdgcn_rcpf(x0 + mu);
+        tau = 2.0f * v0 * v0 * __builtin_amdgcn_rcpf(fmaf(v0, v0, sig));
+        beta = mu;
+      }
+      const float iv0 = sig > 0.0f ? __builtin_amdgcn_rcpf(v0) : 0.0f;
+      const float vi = i == k - 1 ? 1.0f : (i < k - 1 ? x * iv0 : 0.0f);
+      if (i == k) {
+        sD[it][k] = x;
+        sE[it][k - 1] = beta;
+        sTau[it][k] = tau;
+      }
+      if (i < 16 * (tg + 1)) refl[refl_off(k) + i] = vi;
+      float vs[kNG], ws[kNG];
+      segments<B>(vi, vs);
+      // p = tau A v over the leading block
+      // (two partial sums: shorter chains of rounding)
+      float p = 0.0f, p1 = 0.0f;
+      static_range<0, kNG>([&](auto gc) __attribute__((always_inline)) {
+        constexpr int g = decltype(gc)::value;
+        if (g == 0 || g <= tg) {
+          dot8<0>(p, vs[g], *reinterpret_cast<float(*)[8]>(&a[16 * g]));
+          dot8<8>(p1, vs[g], *reinterpret_cast<float(*)[8]>(&a[16 * g + 8]));
+        }
+      });
+      p = i < k ? tau * (p + p1) : 0.0f;
+      const float kc = 0.5f * tau * group_sum<B>(p * vi);
+      const float wi = fmaf(-kc, vi, p);
+      segments<B>(wi, ws);
+      const float nv = -vi, nw = -wi;
+      static_range<0, kNG>([&](auto gc) __attribute__((always_inline)) {
+        constexpr int g = decltype(gc)::value;
+        if (g == 0 || g <= tg) {
+          rank2_8<0>(&a[16 * g], vs[g], ws[g], nv, nw);
+          rank2_8<8>(&a[16 * g + 8], vs[g], ws[g], nv, nw);
+        }
+      });
+    });
   }
-  if (i == B - 1) {
-    sD[it][B - 1] = arow[B - 1];
-    sE[it][B - 1] = 0.0f;
-  }
+  if (i < 2) sD[it][i] = i ? a[1] : a[0];
+  if (i == 1) sE[it][0] = a[0];
+  if (i == B - 1) sE[it][B - 1] = 0.0f;
   __syncthreads();
   sE2[it][i] = i > 0 ? fmaf(sE[it][i - 1], sE[it][i - 1], 0x1p-126f) : 0.0f;
   __syncthreads();
 
-  float lam;
   // ---- the wanted eigenvalues of T (the r largest; all B for the factor output)
   //      by multisection on Sturm counts: q = B / n lanes per eigenvalue, one
   //      point each per step, so a group cuts its interval into q + 1 parts and
   //      a wave ballot gives the part that holds the eigenvalue
+  float lam, tn = 0.0f;
   {
-    float lo = INFINITY, hi = -INFINITY;
-#pragma unroll
-    for (int t = 0; t < B; ++t) {
-      const float el = t > 0 ? fabsf(sE[it][t - 1]) : 0.0f;
-      const float er = t < B - 1 ? fabsf(sE[it][t]) : 0.0f;
-      const float dd = sD[it][t];
-      lo = fminf(lo, dd - el - er);
-      hi = fmaxf(hi, dd + el + er);
+    float lo, hi;
+    {
+      const float el = i > 0 ? fabsf(sE[it][i - 1]) : 0.0f, er = fabsf(sE[it][i]), dd = sD[it][i];
+      lo = -group_max<B>(el + er - dd);
+      hi = group_max<B>(dd + el + er);
+      tn = group_max<B>(fabsf(dd) + el + er);
     }
     const int ne = kFactors ? B : r;
     const int q = B / ne;
@@ -405,6 +450,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void bu
     // 2^-22 of its width (2^-24 for the factor output)
     int steps = 0;
     for (float w = 1.0f; w > (kFactors ? 0x1p-24f : 0x1p-22f); w /= (float)(q + 1)) ++steps;
+#pragma unroll 1
     for (int st = 0; st < steps; ++st) {
       const float hstep = (hi - lo) / (float)(q + 1);
       const float x = fmaf((float)(pi + 1), hstep, lo);
@@ -435,252 +481,268 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void bu
     sLam[it][i] = lam;
   }
   __syncthreads();
-  const float top = fmaxf(sLam[it][0], 0.0f);
-  const float floor_ = fmaxf(kZeroRel * top, kZeroAbs * energy);
-  auto kept = [&](int l) { return l < r && sLam[it][l] > floor_ && sLam[it][l] > 0.0f; };
+  const float floor_ = fmaxf(kZeroRel * fmaxf(sLam[it][0], 0.0f), kZeroAbs * energy);
 
-  // ---- eigenvectors of T for the kept modes: lane l < r runs inverse iteration
-  //      for eigenvalue l on T - lambda_l I = L D L^T (no pivoting; a pivot below
-  //      eps |T| is replaced by eps |T|), every round followed by modified
-  //      Gram-Schmidt over the r vectors (lanes = components)
-  float tn = 0.0f;
+  // ---- eigenvectors of T: lane l < r runs inverse iteration for eigenvalue l on
+  //      T - lambda_l I = L D L^T (no pivoting; a pivot below eps |T| is replaced by
+  //      eps |T|, which only scales the solution); L's entries are e_{t-1} / pivot_{t-1}
+  {
+    const float tiny = fmaxf(tn, 1e-30f) * 1.2e-7f;
+    float Wi[B], X[B];  // reciprocal pivots, the vector
+    auto e_at = [&](int t) { return sE[it][t]; };
+    {
+      // start vector: a fixed sequence that differs between the r vectors
+      float ph = 0.37f * (float)(i + 1);
+      const float stp = 0.6180339f + 0.0917f * (float)i;
 #pragma unroll
-  for (int t = 0; t < B; ++t)
-    tn = fmaxf(tn, fabsf(sD[it][t]) + fabsf(sE[it][t]) + (t > 0 ? fabsf(sE[it][t - 1]) : 0.0f));
-  const float tiny = fmaxf(tn, 1e-30f) * 1.2e-7f;
-  const int lv = i;  // the vector this lane solves for (when i < r)
-  if (lv < r) {
-    float* M = inv(0, it, lv);
-    float* W = inv(1, it, lv);
-    float* X = inv(2, it, lv);
-    const float lv_lam = lam;
-    float pv = sD[it][0] - lv_lam;
-    if (fabsf(pv) < tiny) pv = pv < 0.0f ? -tiny : tiny;
-    W[0] = pv;
-    for (int t = 1; t < B; ++t) {
-      const float el = sE[it][t - 1];
-      const float m = el / pv;
-      pv = (sD[it][t] - lv_lam) - m * el;
+      for (int t = 0; t < B; ++t) {
+        ph = __builtin_amdgcn_fractf(ph + stp);
+        X[t] = fmaf(ph, 1.5f, 1.0f);
+      }
+      float pv = sD[it][0] - lam;
       if (fabsf(pv) < tiny) pv = pv < 0.0f ? -tiny : tiny;
-      M[t] = m;
-      W[t] = pv;
-    }
-    // start vector: a fixed pattern that differs between the r vectors
-    for (int t = 0; t < B; ++t) X[t] = 1.0f + 0.25f * (float)((t * (2 * lv + 3) + lv) % 7);
-  }
-  for (int round = 0; round < kInvRounds; ++round) {
-    if (lv < r) {
-      const float* M = inv(0, it, lv);
-      const float* W = inv(1, it, lv);
-      float* X = inv(2, it, lv);
-      // L y = x, then D z = y, then L^T x = z; scaled to unit max to stay finite
-      float y = X[0];
-      X[0] = y;
+      Wi[0] = __builtin_amdgcn_rcpf(pv);
+#pragma unroll
       for (int t = 1; t < B; ++t) {
-        y = X[t] - M[t] * y;
-        X[t] = y;
+        const float el = e_at(t - 1);
+        pv = fmaf(-el * Wi[t - 1], el, sD[it][t] - lam);
+        if (fabsf(pv) < tiny) pv = pv < 0.0f ? -tiny : tiny;
+        Wi[t] = __builtin_amdgcn_rcpf(pv);
       }
-      float xn = X[B - 1] / W[B - 1];
-      X[B - 1] = xn;
-      float amax = fabsf(xn);
+    }
+#pragma unroll 1
+    for (int round = 0; round < kInvRounds; ++round) {
+      // L y = x, then D z = y, then L^T x = z; scaled to unit max to stay finite
+#pragma unroll
+      for (int t = 1; t < B; ++t) X[t] = fmaf(-(e_at(t - 1) * Wi[t - 1]), X[t - 1], X[t]);
+      X[B - 1] *= Wi[B - 1];
+      float amax = fabsf(X[B - 1]);
+#pragma unroll
       for (int t = B - 2; t >= 0; --t) {
-        xn = X[t] / W[t] - M[t + 1] * xn;
-        X[t] = xn;
-        amax = fmaxf(amax, fabsf(xn));
+        X[t] = fmaf(-e_at(t), X[t + 1], X[t]) * Wi[t];
+        amax = fmaxf(amax, fabsf(X[t]));
       }
-      const float sc = amax > 0.0f ? 1.0f / amax : 1.0f;
-      for (int t = 0; t < B; ++t) X[t] *= sc;
-    }
-    __syncthreads();
-    // modified Gram-Schmidt over the vectors in eigenvalue order; lane i holds
-    // component i.  Vectors past r are zero and stay zero, so every loop runs at
-    // the full width without a branch and the lane reductions can overlap.
-    float xr[kMaxR];
+      const float sc = amax > 0.0f ? __builtin_amdgcn_rcpf(amax) : 1.0f;
+      if (i < r) {
 #pragma unroll
-    for (int l = 0; l < kMaxR; ++l) xr[l] = l < r ? inv(2, it, l)[i] : 0.0f;
-#pragma unroll
-    for (int l = 0; l < kMaxR; ++l) {
-#pragma unroll
-      for (int m = 0; m < l; ++m) {
-        const float d = group_sum<B>(xr[l] * xr[m]);
-        xr[l] = fmaf(-d, xr[m], xr[l]);
+        for (int q = 0; q < B / 4; ++q)
+          *reinterpret_cast<float4*>(&sX[it][i][4 * q]) =
+              make_float4(X[4 * q] * sc, X[4 * q + 1] * sc, X[4 * q + 2] * sc, X[4 * q + 3] * sc);
       }
-      const float nn = group_sum<B>(xr[l] * xr[l]);
-      xr[l] = nn > 0.0f ? xr[l] * __builtin_amdgcn_rsqf(nn) : 0.0f;
-    }
+      __syncthreads();
+      // modified Gram-Schmidt over the vectors in eigenvalue order; lane i holds
+      // component i (right-looking: a final vector is projected out of every later
+      // one at once, their lane reductions overlapping; vectors past r are zero)
+      float xr[kMaxR];
 #pragma unroll
-    for (int l = 0; l < kMaxR; ++l)
-      if (l < r) inv(2, it, l)[i] = xr[l];
-    __syncthreads();
+      for (int l = 0; l < kMaxR; ++l) xr[l] = l < r ? sX[it][l][i] : 0.0f;
+      static_range<0, kMaxR>([&](auto mc) __attribute__((always_inline)) {
+        constexpr int m = decltype(mc)::value;
+        const float nn = group_sum<B>(xr[m] * xr[m]);
+        xr[m] = nn > 0.0f ? xr[m] * __builtin_amdgcn_rsqf(nn) : 0.0f;
+        if constexpr (m + 1 < kMaxR) {
+          float d[kMaxR - 1 - m];
+#pragma unroll
+          for (int l = m + 1; l < kMaxR; ++l) d[l - m - 1] = xr[l] * xr[m];
+          group_sums<B, kMaxR - 1 - m>(d);
+#pragma unroll
+          for (int l = m + 1; l < kMaxR; ++l) xr[l] = fmaf(-d[l - m - 1], xr[m], xr[l]);
+        }
+      });
+      __syncthreads();
+#pragma unroll
+      for (int l = 0; l < (kMaxR <= 8 ? 8 : 16); ++l) sX[it][l][i] = l < kMaxR ? xr[l] : 0.0f;
+      __syncthreads();
+      if (round + 1 < kInvRounds) {
+        const int iv = i < r ? i : 0;
+#pragma unroll
+        for (int q = 0; q < B / 4; ++q) {
+          const float4 v = *reinterpret_cast<const float4*>(&sX[it][iv][4 * q]);
+          X[4 * q] = v.x;
+          X[4 * q + 1] = v.y;
+          X[4 * q + 2] = v.z;
+          X[4 * q + 3] = v.w;
+        }
+        __syncthreads();
+      }
+    }
   }
 
-  // ---- back-transformation: u_l = H_0 H_1 ... H_{B-3} x_l, lane i component i
-  float u[kMaxR];
+  // ---- back-transformation u_l = H_{B-1} ... H_3 H_2 x_l: lane (it, l, c) holds
+  //      components kCPL c .. of vector l
+  {
+    const int l = i / kLPV, c = i % kLPV;
+    float y[kCPL];
 #pragma unroll
-  for (int l = 0; l < kMaxR; ++l) u[l] = l < r ? inv(2, it, l)[i] : 0.0f;
-  // (column k of row i holds v_k[i] for i > k + 1)
-  // (vectors past r are zero and stay zero: no branch, the kMaxR reductions overlap)
-  for (int k = B - 3; k >= 0; --k) {
-    const float vi = i == k + 1 ? 1.0f : (i > k + 1 ? arow[k] : 0.0f);
-    const float tau = sTau[it][k];
-    float dd[kMaxR];
+    for (int m = 0; m < kCPL; m += 4) {
+      const float4 v = *reinterpret_cast<const float4*>(&sX[it][l][kCPL * c + m]);
+      y[m] = v.x;
+      y[m + 1] = v.y;
+      y[m + 2] = v.z;
+      y[m + 3] = v.w;
+    }
+#pragma unroll 4
+    for (int k = 2; k < B; ++k) {
+      const bool in = kCPL * c < 16 * (((k - 1) >> 4) + 1);  // inside the stored reflector
+      const float* v = refl + refl_off(k) + (in ? kCPL * c : 0);
+      const float tau = in ? sTau[it][k] : 0.0f;
+      float x[kCPL];
 #pragma unroll
-    for (int l = 0; l < kMaxR; ++l) dd[l] = group_sum<B>(vi * u[l]);
+      for (int m = 0; m < kCPL; m += 4) {
+        const float4 w = *reinterpret_cast<const float4*>(v + m);
+        x[m] = w.x;
+        x[m + 1] = w.y;
+        x[m + 2] = w.z;
+        x[m + 3] = w.w;
+      }
+      float d0 = 0.0f, d1 = 0.0f;
 #pragma unroll
-    for (int l = 0; l < kMaxR; ++l) u[l] = fmaf(-tau * dd[l], vi, u[l]);
+      for (int m = 0; m < kCPL; m += 2) {
+        d0 = fmaf(x[m], y[m], d0);
+        d1 = fmaf(x[m + 1], y[m + 1], d1);
+      }
+      float d = in ? d0 + d1 : 0.0f;
+      d += dpp_f<0xB1>(d);
+      if (kLPV >= 4) d += dpp_f<0x4E>(d);
+      if (kLPV >= 8) d += dpp_f<0x141>(d);
+      const float f = -tau * d;
+#pragma unroll
+      for (int m = 0; m < kCPL; ++m) y[m] = fmaf(f, x[m], y[m]);
+    }
+    __syncthreads();  // the reflectors are no longer read: U takes their LDS
+    if (l < kMaxR) {
+#pragma unroll
+      for (int m = 0; m < kCPL; ++m) sBig[(it * B + kCPL * c + m) * kUS + l] = y[m];
+    }
   }
-  __syncthreads();  // the reflectors are no longer read: U takes their LDS
-  float* sU = reinterpret_cast<float*>(sBuf);  // [kI][B][kMaxR + 1]
-  auto U_at = [&](int t, int row, int l) -> float& { return sU[(t * B + row) * (kMaxR + 1) + l]; };
+  __syncthreads();
+  auto U_at = [&](int t, int row, int l) { return sBig[(t * B + row) * kUS + l]; };
+
+  // ---- basis columns V[:, l] = D^T u_l / sigma_l on fp32 MFMA 16x16x4: rows are the
+  //      vectors, columns the dims 8 l16 + T of tile T, K the tokens 4 s + q4, whose keys
+  //      the lane reads 16 bytes at a time (cache-resident).  Ranks up to 8 put item t's
+  //      vectors in rows 8 t .. 8 t + 7, so both items of a 32-token wave share the
+  //      accumulators; then sign, quantisation and packing of four vectors per lane.
+  const int stride = rec_stride(r, 0, B);
+  float fl[kI];
 #pragma unroll
-  for (int l = 0; l < kMaxR; ++l)
-    if (l < r) U_at(it, i, l) = u[l];
+  for (int t = 0; t < kI; ++t) fl[t] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(floor_), t * B));
+  constexpr int kPassItems = kMaxR <= 8 ? kI : 1;  // items per pass
+#pragma unroll
+  for (int t0 = 0; t0 < kI; t0 += kPassItems) {
+    f4 acc[8];
+#pragma unroll
+    for (int T = 0; T < 8; ++T) acc[T] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int t = t0; t < t0 + kPassItems; ++t) {
+      float mu8[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) mu8[e] = sMu[t][8 * l16 + e];
+      const int ur = kPassItems > 1 ? l16 - 8 * t : l16;   // vector of this lane's A row
+      const bool uok = ur >= 0 && ur < kMaxR;
+#pragma unroll
+      for (int s = 0; s < B / 4; ++s) {
+        const float uv = uok ? U_at(t, 4 * s + q4, uok ? ur : 0) : 0.0f;
+        float x[8];
+#pragma unroll
+        for (int u = 0; u < 8 / kVec; ++u)
+          chunk_to_f<KT>(key16(t, 4 * s + q4, 8 * l16 + u * kVec), &x[u * kVec]);
+#pragma unroll
+        for (int T = 0; T < 8; ++T)
+          acc[T] = __builtin_amdgcn_mfma_f32_16x16x4f32(uv, x[T] - mu8[T], acc[T], 0, 0, 0);
+      }
+    }
+    const int pt = kPassItems > 1 ? q4 >> 1 : t0;              // this lane's item
+    const int lb = kPassItems > 1 ? 4 * (q4 & 1) : 4 * q4;     // its first vector
+    const bool act = kI > 1 && kPassItems > 1 ? (pt ? item[kI - 1].active : item[0].active) : item[t0].active;
+    const long orow = kI > 1 && kPassItems > 1 ? (pt ? item[kI - 1].row : item[0].row) : item[t0].row;
+    const int oe = kI > 1 && kPassItems > 1 ? (pt ? item[kI - 1].e : item[0].e) : item[t0].e;
+    const int oh = kI > 1 && kPassItems > 1 ? (pt ? item[kI - 1].h : item[0].h) : item[t0].h;
+    const float fle = kI > 1 && kPassItems > 1 ? (pt ? fl[kI - 1] : fl[0]) : fl[t0];
+    uint8_t* rec = summaries + orow * (long)stride;
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      const int l = lb + jj;
+      if (l >= r) continue;
+      const float lv = sLam[pt][l];
+      const bool kl = lv > fle && lv > 0.0f;
+      const float isig = kl ? 1.0f / sqrtf(lv) : 0.0f;
+      float v[8], best = -1.0f, bval = 0.0f;
+      int bidx = 0;
+#pragma unroll
+      for (int T = 0; T < 8; ++T) {
+        v[T] = acc[T][jj] * isig;
+        const float av = fabsf(v[T]);
+        if (av > best) { best = av; bidx = 8 * l16 + T; bval = v[T]; }
+      }
+      // sign convention: the largest |V[c][l]| (lowest c on ties) is made positive:
+      // the largest magnitude over the row, then the lowest dim holding it, its sign in
+      // the low bit
+      const float gbest = row_max(best);
+      const int key = row_min_int(best == gbest ? 2 * bidx + (bval < 0.0f ? 1 : 0) : 0x7fffffff);
+      const float flip = (key & 1) ? -1.0f : 1.0f;
+      if (l16 == 0) sFlip[pt][l] = flip;
+      if (kFactors) {
+        if (act) {
+          float* bo = basis_out + ((long)oe * H_kv + oh) * kDim * r;
+#pragma unroll
+          for (int T = 0; T < 8; ++T) bo[(8 * l16 + T) * r + l] = flip * v[T];
+        }
+      } else {
+        const float vsc = f16_scale(gbest, 7.0f);
+        const float ivs = inv_scale(vsc);
+        uint32_t word = 0;
+#pragma unroll
+        for (int T = 0; T < 8; ++T) word |= (uint32_t)(quant(flip * v[T], ivs, 7) + 8) << (4 * T);
+        if (act) {
+          *reinterpret_cast<uint32_t*>(rec + 64 * l + 4 * l16) = word;
+          if (l16 == 0) *reinterpret_cast<uint16_t*>(rec + rec_scale_off(r, 0, B) + 2 * l) = f16_bits(vsc);
+        }
+      }
+    }
+  }
   __syncthreads();
 
-  // ---- basis columns V[:, l] = D^T u_l / sigma_l over this lane's kCols columns;
-  //      the key rows come back from global memory (cache-resident), every row's
-  //      slice requested before the first is used
-  constexpr int kC = P::kCols;
-  constexpr int kW = kC * (int)sizeof(KT) / 4;  // 32-bit words of a row slice
-  uint32_t ksl[B][kW];
-  {
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(kpage + kC * i);
-    constexpr int kRowW = kDim * (int)sizeof(KT) / 4;
-#pragma unroll
-    for (int t = 0; t < B; ++t) {
-      if constexpr (kW == 4) {
-        const uint4 w = active ? *reinterpret_cast<const uint4*>(src + t * kRowW) : make_uint4(0, 0, 0, 0);
-        ksl[t][0] = w.x; ksl[t][1] = w.y; ksl[t][2] = w.z; ksl[t][3] = w.w;
-      } else if constexpr (kW == 2) {
-        const uint2 w = active ? *reinterpret_cast<const uint2*>(src + t * kRowW) : make_uint2(0, 0);
-        ksl[t][0] = w.x; ksl[t][1] = w.y;
-      } else {
-        ksl[t][0] = active ? src[t * kRowW] : 0u;
-      }
-    }
-  }
-  float mu_c[kC];
-#pragma unroll
-  for (int cc = 0; cc < kC; ++cc) mu_c[cc] = sMu[it][kC * i + cc];
-  float vcol[kMaxR][kC];
-#pragma unroll
-  for (int l = 0; l < kMaxR; ++l)
-#pragma unroll
-    for (int cc = 0; cc < kC; ++cc) vcol[l][cc] = 0.0f;
-#pragma unroll
-  for (int t = 0; t < B; ++t) {
-    float kv[kC];
-#pragma unroll
-    for (int cc = 0; cc < kC; ++cc) {
-      float x;
-      if constexpr (sizeof(KT) == 2)
-        x = __uint_as_float((cc & 1) ? (ksl[t][cc >> 1] & 0xffff0000u) : (ksl[t][cc >> 1] << 16));
-      else
-        x = __uint_as_float(ksl[t][cc]);
-      kv[cc] = x - mu_c[cc];
-    }
-#pragma unroll
-    for (int l = 0; l < kMaxR; ++l) {
-      if (l < r) {
-        const float ul = U_at(it, t, l);
-#pragma unroll
-        for (int cc = 0; cc < kC; ++cc) vcol[l][cc] = fmaf(kv[cc], ul, vcol[l][cc]);
-      }
-    }
-  }
-  // sign convention: the largest |V[c][l]| (lowest c on ties) is made positive:
-  // the largest magnitude over the item, then the lowest column holding it, its
-  // sign in the low bit
-  float best_abs[kMaxR];
+  // ---- coefficient row i: C[i][l] = flip_l u_l[i] sigma_l (0 for a dropped mode)
+  const bool act = kI > 1 ? (it ? item[kI - 1].active : item[0].active) : item[0].active;
+  if (!act) return;
+  const long orow = kI > 1 ? (it ? item[kI - 1].row : item[0].row) : item[0].row;
+  float crow[kMaxR], cabs = 0.0f;
 #pragma unroll
   for (int l = 0; l < kMaxR; ++l) {
-    best_abs[l] = 0.0f;
-    if (l >= r) continue;
-    const bool kl = kept(l);
-    const float sig = kl ? sqrtf(sLam[it][l]) : 1.0f;
-    float best = -1.0f, bval = 0.0f;
-    int bidx = 0;
-#pragma unroll
-    for (int cc = 0; cc < kC; ++cc) {
-      vcol[l][cc] = kl ? vcol[l][cc] / sig : 0.0f;
-      const float av = fabsf(vcol[l][cc]);
-      if (av > best) { best = av; bidx = kC * i + cc; bval = vcol[l][cc]; }
-    }
-    const float gbest = group_max<B>(best);
-    const int key = group_min_int<B>(best == gbest ? 2 * bidx + (bval < 0.0f ? 1 : 0) : 0x7fffffff);
-    best = gbest;
-    const float flip = (key & 1) ? -1.0f : 1.0f;
-    if (i == 0) sFlip[it][l] = flip;
-#pragma unroll
-    for (int cc = 0; cc < kC; ++cc) vcol[l][cc] *= flip;
-    best_abs[l] = best;
+    const float lv = sLam[it][l];
+    const bool kl = l < r && lv > floor_ && lv > 0.0f;
+    crow[l] = kl ? sFlip[it][l] * U_at(it, i, l) * sqrtf(lv) : 0.0f;
+    cabs = fmaxf(cabs, fabsf(crow[l]));
   }
-  __syncthreads();
-  // coefficient row i: C[i][l] = flip_l u_l[i] sigma_l (0 for a dropped mode)
-  float crow[kMaxR];
-#pragma unroll
-  for (int l = 0; l < kMaxR; ++l)
-    crow[l] = (l < r && kept(l)) ? sFlip[it][l] * u[l] * sqrtf(sLam[it][l]) : 0.0f;
-
+  constexpr int kC = kDim / B;  // centroid elements of this lane
   if (kFactors) {
-    if (!active) return;
-    const long out_item = (long)e * H_kv + h;
+    const long oi = (long)(kI > 1 ? (it ? item[kI - 1].e : item[0].e) : item[0].e) * H_kv +
+                    (kI > 1 ? (it ? item[kI - 1].h : item[0].h) : item[0].h);
 #pragma unroll
-    for (int cc = 0; cc < kC; ++cc) mu_out[out_item * kDim + kC * i + cc] = sMu[it][kC * i + cc];
-#pragma unroll
-    for (int l = 0; l < kMaxR; ++l) {
-      if (l >= r) continue;
-#pragma unroll
-      for (int cc = 0; cc < kC; ++cc)
-        basis_out[(out_item * kDim + kC * i + cc) * r + l] = vcol[l][cc];
-    }
+    for (int cc = 0; cc < kC; ++cc) mu_out[oi * kDim + kC * i + cc] = sMu[it][kC * i + cc];
 #pragma unroll
     for (int l = 0; l < kMaxR; ++l)
-      if (l < r) coef_out[(out_item * B + i) * r + l] = crow[l];
-    sigma2_out[out_item * B + i] = fmaxf(sLam[it][i], 0.0f);
+      if (l < r) coef_out[(oi * B + i) * r + l] = crow[l];
+    sigma2_out[oi * B + i] = fmaxf(sLam[it][i], 0.0f);
     return;
   }
-
-  // ---- quantise and pack the record in LDS, then copy it out with 16-byte stores
-  const int stride = rec_stride(r, basis, B);
-  uint8_t* sRec = sBuf + it * stride;
-  const int scale_off = rec_scale_off(r, basis, B);
+  uint8_t* rec = summaries + orow * (long)stride;
+  const int scale_off = rec_scale_off(r, 0, B);
+  {
+    const float cs = f16_scale(cabs, 127.0f);
+    uint8_t* dst = rec + rec_coef_off(r) + i * r;
+    if (kMaxR == 8 && r == 8) {
+      uint32_t w[2] = {0u, 0u};
 #pragma unroll
-  for (int l = 0; l < kMaxR; ++l) {
-    if (l >= r) continue;
-    if (basis == LOCKS_BASIS_INT4) {
-      const float vs = f16_scale(best_abs[l], 7.0f);
-      uint32_t word = 0;
-#pragma unroll
-      for (int cc = 0; cc < kC; ++cc) word |= (uint32_t)(quant(vcol[l][cc], vs, 7) + 8) << (4 * cc);
-      uint8_t* dst = sRec + 64 * l + (kC / 2) * i;
-#pragma unroll
-      for (int bb = 0; bb < kC / 2; ++bb) dst[bb] = (uint8_t)(word >> (8 * bb));
-      if (i == 0) *reinterpret_cast<uint16_t*>(sRec + scale_off + 2 * l) = f16_bits(vs);
-    } else if (basis == LOCKS_BASIS_INT8) {
-      const float vs = f16_scale(best_abs[l], 127.0f);
-#pragma unroll
-      for (int cc = 0; cc < kC; ++cc)
-        sRec[128 * l + kC * i + cc] = (uint8_t)(quant(vcol[l][cc], vs, 127) + 128);
-      if (i == 0) *reinterpret_cast<uint16_t*>(sRec + scale_off + 2 * l) = f16_bits(vs);
+      for (int l = 0; l < 8; ++l) w[l >> 2] |= (uint32_t)(quant_div(crow[l], cs, 127) + 128) << (8 * (l & 3));
+      *reinterpret_cast<uint2*>(dst) = make_uint2(w[0], w[1]);
     } else {
 #pragma unroll
-      for (int cc = 0; cc < kC; ++cc)
-        *reinterpret_cast<uint16_t*>(sRec + 256 * l + 2 * (kC * i + cc)) =
-            (uint16_t)bf16_rne_bits(vcol[l][cc]);
-      if (i == 0) *reinterpret_cast<uint16_t*>(sRec + scale_off + 2 * l) = f16_bits(1.0f);
+      for (int l = 0; l < kMaxR; ++l)
+        if (l < r) dst[l] = (uint8_t)(quant_div(crow[l], cs, 127) + 128);
     }
-  }
-  {
-    float cabs = 0.0f;
-#pragma unroll
-    for (int l = 0; l < kMaxR; ++l) cabs = fmaxf(cabs, fabsf(crow[l]));
-    const float cs = f16_scale(cabs, 127.0f);
-    const int coef_off = rec_coef_off(r, basis);
-#pragma unroll
-    for (int l = 0; l < kMaxR; ++l)
-      if (l < r) sRec[coef_off + i * r + l] = (uint8_t)(quant(crow[l], cs, 127) + 128);
-    *reinterpret_cast<uint16_t*>(sRec + scale_off + 2 * (r + i)) = f16_bits(cs);
+    *reinterpret_cast<uint16_t*>(rec + scale_off + 2 * (r + i)) = f16_bits(cs);
   }
   {
     float m = 0.0f;
@@ -688,18 +750,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void bu
     for (int cc = 0; cc < kC; ++cc) m = fmaxf(m, fabsf(sMu[it][kC * i + cc]));
     m = group_max<B>(m);
     const float ms = f16_scale(m, 127.0f);
-    const int mu_off = rec_mu_off(r, basis, B);
+    uint32_t w = 0;
 #pragma unroll
-    for (int cc = 0; cc < kC; ++cc)
-      sRec[mu_off + kC * i + cc] = (uint8_t)(quant(sMu[it][kC * i + cc], ms, 127) + 128);
-    if (i == 0) *reinterpret_cast<uint16_t*>(sRec + scale_off + 2 * (r + B)) = f16_bits(ms);
+    for (int cc = 0; cc < kC; ++cc) w |= (uint32_t)(quant_div(sMu[it][kC * i + cc], ms, 127) + 128) << (8 * cc);
+    uint8_t* dst = rec + rec_mu_off(r, 0, B) + kC * i;
+    if (kC == 4) *reinterpret_cast<uint32_t*>(dst) = w;
+    else *reinterpret_cast<uint16_t*>(dst) = (uint16_t)w;
+    if (i == 0) *reinterpret_cast<uint16_t*>(rec + scale_off + 2 * (r + B)) = f16_bits(ms);
   }
-  for (int o = rec_payload(r, basis, B) + i; o < stride; o += B) sRec[o] = 0;
-  __syncthreads();
-  if (!active) return;
-  uint8_t* rec = summaries + (blk * H_kv + h) * (long)stride;
-  for (int o = 16 * i; o < stride; o += 16 * B)
-    *reinterpret_cast<uint4*>(rec + o) = *reinterpret_cast<const uint4*>(sRec + o);
+  if (rec_payload(r, 0, B) + i < stride) rec[rec_payload(r, 0, B) + i] = 0;
 }
 
 }  // namespace
@@ -715,6 +774,7 @@ hipError_t launch_build_page(const locks_cfg_t& c, const void* k_cache, const in
   const int per = 64 / c.page_size;
   const long blocks = (items + per - 1) / per;
   if (blocks > 0x7fffffffL) return hipErrorInvalidConfiguration;
+  if (c.basis != LOCKS_BASIS_INT4) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks), block(64);
   // ranks up to 8 take the instance whose rank-sized arrays (LDS and registers)
   // hold 8 vectors: its smaller LDS fits more waves per compute unit
@@ -722,7 +782,7 @@ hipError_t launch_build_page(const locks_cfg_t& c, const void* k_cache, const in
   hipLaunchKernelGGL((build_page_kernel<KT, BP, F, MR>), grid, block, 0, st, c.num_seqs,        \
                      c.num_kv_heads, c.max_pages_per_seq, c.rank, static_cast<const KT*>(k_cache), \
                      page_table, seq_lens, build_list, n_items, (int)all_pages,                \
-                     (uint8_t*)summaries, mu, basis, coef, sigma2, c.basis)
+                     (uint8_t*)summaries, mu, basis, coef, sigma2)
 #define LOCKS_BUILD_PAGE(KT, BP, F)                                                            \
   if (c.rank <= 8) LOCKS_BUILD_PAGE_R(KT, BP, F, 8); else LOCKS_BUILD_PAGE_R(KT, BP, F, kMaxRank)
 #define LOCKS_BUILD_PAGE_B(KT)                                                                 \

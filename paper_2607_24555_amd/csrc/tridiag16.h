@@ -32,7 +32,7 @@ constexpr int kXRow = 20;  // LDS stride (floats) of one vector in the scratch
 
 template <int C>
 __device__ __forceinline__ float dpp(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), C, 0xF, 0xF, false));
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), C, 0xF, 0xF, true));
 }
 // the value of lane K of this lane's 16-lane row
 template <int K>
