@@ -22,6 +22,11 @@
 //    yields an orthonormal basis of its eigenspace).
 //  * Back-transformation with kCPL components of one vector per lane: a reflector is one
 //    short dot product, a few lane exchanges and one update.
+// Bound: VALU issue (the Householder steps are about half of it) at four waves per SIMD
+// for 32 tokens and three for 64, which the registers of the inverse iteration and the
+// packed reflectors in LDS are held to.  2 x 128K tokens x 8 heads at r = 8: 748 us at 32
+// tokens and 1,526 at 64, where Gram rows in LDS, eigenvectors solved through LDS by r
+// lanes and one reduction at a time took 1,470 and 3,900.
 #include "build_common.h"
 #include "locks_internal.h"
 
@@ -172,10 +177,10 @@ __device__ __forceinline__ void static_range(F&& f) {
   }
 }
 
-// Reflector of column k (rows 0 .. k - 1): 16 (seg + 1) floats, seg = (k - 1) / 16.
+// Reflector of column k >= 2 (rows 0 .. k - 1): 16 (seg + 1) floats, seg = (k - 1) / 16.
 __device__ __forceinline__ int refl_off(int k) {
   const int seg = (k - 1) >> 4;
-  return 128 * seg * (seg + 1) + 16 * (seg + 1) * ((k - 1) & 15);
+  return 128 * seg * (seg + 1) + 16 * (seg + 1) * ((k - 1) & 15) - 16;
 }
 
 // One (page, KV head) of the block; uniform over the wave.
@@ -186,7 +191,7 @@ struct PageItem {
 };
 
 template <typename KT, int B, bool kFactors, int kMaxR>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(B == 32 && kMaxR <= 8 ? 4 : 2))) void build_page_kernel(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(B == 32 && kMaxR <= 8 ? 4 : (kMaxR <= 8 ? 3 : 2)))) void build_page_kernel(
     int S, int H_kv, int max_pages, int r, const KT* __restrict__ k_cache,
     const int32_t* __restrict__ page_table, const int32_t* __restrict__ seq_lens,
     const int32_t* __restrict__ build_list, int n_items, int all_pages,
@@ -200,17 +205,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(B == 32 && k
   constexpr int kLPV = B / kCPL;              // lanes per vector
   constexpr int kUS = kMaxR <= 8 ? 9 : 17;    // LDS stride (floats) of a row of U
   // LDS phases of sBig: 32 Gram rows at a time (layout change), the reflectors, U
-  constexpr int kGramF = 32 * kPad, kReflF = kI * 128 * kNG * (kNG + 1), kUF = kI * B * kUS;
+  constexpr int kGramF = 32 * kPad, kReflF = kI * (128 * kNG * (kNG + 1) - 16), kUF = kI * B * kUS;
   constexpr int kBig0 = kGramF > kReflF ? kGramF : kReflF;
   __shared__ __align__(16) float sBig[kBig0 > kUF ? kBig0 : kUF];
   __shared__ __align__(16) float sX[kI][kMaxR <= 8 ? 8 : 16][kPad];  // eigenvectors of T
   __shared__ __align__(16) float sMu[kI][kDim];
   __shared__ __align__(16) float sD[kI][B];   // diagonal of T
   __shared__ __align__(16) float sE[kI][B];   // off-diagonal of T (e[k] couples k, k + 1)
-  __shared__ __align__(16) float sE2[kI][B];  // e[k - 1]^2 (Sturm counts)
-  __shared__ float sTau[kI][B];
   __shared__ float sLam[kI][B];               // eigenvalues, descending
-  __shared__ float sFlip[kI][16];
+  // e[k - 1]^2 (Sturm counts) before the eigenvectors take sX; the flips after sD is read
+  auto& sE2 = *reinterpret_cast<float(*)[kI][B]>(&sX[0][0][0]);
+  auto& sFlip = *reinterpret_cast<float(*)[kI][16]>(&sD[0][0]);
 
   const int lane = threadIdx.x;
   const int it = lane / B, i = lane % B;
@@ -242,11 +247,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(B == 32 && k
   }
   if (!any) return;
   auto kpage = [&](int t) { return k_cache + item[t].row * (long)B * kDim; };
-  // 16 bytes of token `tok` of item t from element c (zeros for an inactive item)
-  auto key16 = [&](int t, int tok, int c) {
-    return item[t].active ? *reinterpret_cast<const uint4*>(kpage(t) + tok * kDim + c)
-                          : make_uint4(0, 0, 0, 0);
+  // 16 bytes of item t at token tok0 (uniform) and lane offset `off` bytes (zeros for an
+  // inactive item)
+  auto key16 = [&](int t, int tok0, uint32_t off) {
+    const char* p = reinterpret_cast<const char*>(kpage(t) + tok0 * kDim);
+    return item[t].active ? *reinterpret_cast<const uint4*>(p + off) : make_uint4(0, 0, 0, 0);
   };
+  constexpr uint32_t kEl = sizeof(KT);
+  const uint32_t off_row = (uint32_t)(q4 * kDim + 8 * l16) * kEl;      // token q4, dims 8 l16 ..
+  const uint32_t off_op = (uint32_t)(l16 * kDim + kVec * q4) * kEl;   // row l16, columns kVec q4 ..
 
   // ---- centroid and mean squared norm: lane (q4, l16) sums dims 8 l16 .. + 7 over the
   //      tokens 4 s + q4, pairwise (exact for equal rows), then over q4
@@ -258,10 +267,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(B == 32 && k
     float part[5][8];
 #pragma unroll
     for (int s = 0; s < B / 4; ++s) {
+      if (s % 8 == 0) __builtin_amdgcn_sched_barrier(0);  // bounds the loads in flight
       float x[8];
 #pragma unroll
       for (int u = 0; u < 8 / kVec; ++u)
-        chunk_to_f<KT>(key16(t, 4 * s + q4, 8 * l16 + u * kVec), &x[u * kVec]);
+        chunk_to_f<KT>(key16(t, 4 * s, off_row + 16u * u), &x[u * kVec]);
 #pragma unroll
       for (int e = 0; e < 8; ++e) en = fmaf(x[e], x[e], en);
       int lvl = 0;
@@ -292,7 +302,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(B == 32 && k
   //      holds G[16 T + 4 q4 + jj][16 U + l16].  Row i goes to lane i through LDS, 32
   //      rows of an item at a time.
   float a[B];
+  int ex = 0;  // the rows are scaled by 2^-ex, so that the trace lies in [1/2, 1)
   {
+    float dg = 0.0f;
     constexpr int kTiles = kNG * (kNG + 1) / 2;
     f4 acc[kI][kTiles];
 #pragma unroll
@@ -301,10 +313,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(B == 32 && k
       for (int n = 0; n < kTiles; ++n) acc[t][n] = f4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
       for (int ch = 0; ch < kDim / (4 * kVec); ++ch) {
+        if (B == 64) __builtin_amdgcn_sched_barrier(0);
         const int c0 = kVec * (4 * ch + q4);
         float x[kNG][kVec];
 #pragma unroll
-        for (int T = 0; T < kNG; ++T) chunk_to_f<KT>(key16(t, 16 * T + l16, c0), x[T]);
+        for (int T = 0; T < kNG; ++T) chunk_to_f<KT>(key16(t, 16 * T, off_op + 64u * ch), x[T]);
 #pragma unroll
         for (int m = 0; m < kVec; ++m) {
           const float mu = sMu[t][c0 + m];
@@ -342,6 +355,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(B == 32 && k
       __syncthreads();
       const bool mine = (lane >> 5) == st;
       const float* row = sBig + (lane & 31) * kPad;
+      if (mine) dg = row[i];
 #pragma unroll
       for (int q = 0; q < B / 4; ++q) {
         const float4 v = *reinterpret_cast<const float4*>(row + 4 * q);
@@ -354,13 +368,20 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(B == 32 && k
       }
       __syncthreads();
     }
+    const float tr = group_sum<B>(dg);
+    ex = tr > 0.0f && tr < INFINITY ? __builtin_amdgcn_frexp_expf(tr) : 0;
+#pragma unroll
+    for (int j = 0; j < B; ++j) a[j] = __builtin_amdgcn_ldexpf(a[j], -ex);
   }
 
   // ---- Householder reduction to tridiagonal form.  Step k annihilates column k above
   //      row k - 1 with H = I - tau v v^T (v_{k-1} = 1) and updates the leading block by
   //      the rank-2 form A - v w^T - w v^T.  v and w are zero at rows >= k, so whole
   //      16-column groups run without a mask (the skipped products are exact zeros).
-  float* refl = sBig + it * 128 * kNG * (kNG + 1);
+  //      A column whose entries above row k - 1 are below 2^-40 of the trace counts as
+  //      reduced: the rounding residue of a page of few modes shrinks step by step
+  //      towards the denormals, where the hardware reciprocals overflow.
+  float* refl = sBig + it * (128 * kNG * (kNG + 1) - 16);
 #pragma unroll 1
   for (int t = kNG - 1; t >= 0; --t) {
     static_range<0, 16>([&](auto sc) __attribute__((always_inline)) {
@@ -378,20 +399,22 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(B == 32 && k
       }
       const float sig = group_sum<B>(i < k - 1 ? x * x : 0.0f);
       float tau = 0.0f, v0 = 1.0f, beta = x0;
-      if (sig > 0.0f) {
+      if (sig > 0x1p-80f) {
         const float mu = __builtin_amdgcn_sqrtf(fmaf(x0, x0, sig));
         v0 = x0 <= 0.0f ? x0 - mu : -sig * __builtin_amdgcn_rcpf(x0 + mu);
         tau = 2.0f * v0 * v0 * __builtin_amdgcn_rcpf(fmaf(v0, v0, sig));
         beta = mu;
       }
-      const float iv0 = sig > 0.0f ? __builtin_amdgcn_rcpf(v0) : 0.0f;
+      const float iv0 = sig > 0x1p-80f ? __builtin_amdgcn_rcpf(v0) : 0.0f;
       const float vi = i == k - 1 ? 1.0f : (i < k - 1 ? x * iv0 : 0.0f);
       if (i == k) {
         sD[it][k] = x;
         sE[it][k - 1] = beta;
-        sTau[it][k] = tau;
       }
-      if (i < 16 * (tg + 1)) refl[refl_off(k) + i] = vi;
+      // (kept as sqrt(tau) v: the back-transformation's H is then I - v v^T; the root
+      // refined by one Newton step, 0 for tau = 0)
+      const float ty = __builtin_amdgcn_rsqf(fmaxf(tau, 0x1p-126f)), ts = tau * ty;
+      if (i < 16 * (tg + 1)) refl[refl_off(k) + i] = vi * fmaf(fmaf(-ts, ts, tau), 0.5f * ty, ts);
       float vs[kNG], ws[kNG];
       segments<B>(vi, vs);
       // p = tau A v over the leading block
@@ -478,7 +501,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(B == 32 && k
     }
     const float lam_g = 0.5f * (lo + hi);
     lam = __shfl(lam_g, it * B + (i < ne ? i : ne - 1) * q, 64);
-    sLam[it][i] = lam;
+    sLam[it][i] = __builtin_amdgcn_ldexpf(lam, ex);
   }
   __syncthreads();
   const float floor_ = fmaxf(kZeroRel * fmaxf(sLam[it][0], 0.0f), kZeroAbs * energy);
@@ -505,6 +528,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(B == 32 && k
 #pragma unroll
       for (int t = 1; t < B; ++t) {
         const float el = e_at(t - 1);
+        if (t % 8 == 0) __builtin_amdgcn_sched_barrier(0);  // bounds the T entries in flight
         pv = fmaf(-el * Wi[t - 1], el, sD[it][t] - lam);
         if (fabsf(pv) < tiny) pv = pv < 0.0f ? -tiny : tiny;
         Wi[t] = __builtin_amdgcn_rcpf(pv);
@@ -514,11 +538,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(B == 32 && k
     for (int round = 0; round < kInvRounds; ++round) {
       // L y = x, then D z = y, then L^T x = z; scaled to unit max to stay finite
 #pragma unroll
-      for (int t = 1; t < B; ++t) X[t] = fmaf(-(e_at(t - 1) * Wi[t - 1]), X[t - 1], X[t]);
+      for (int t = 1; t < B; ++t) {
+        if (t % 8 == 0) __builtin_amdgcn_sched_barrier(0);
+        X[t] = fmaf(-(e_at(t - 1) * Wi[t - 1]), X[t - 1], X[t]);
+      }
       X[B - 1] *= Wi[B - 1];
       float amax = fabsf(X[B - 1]);
 #pragma unroll
       for (int t = B - 2; t >= 0; --t) {
+        if (t % 8 == 0) __builtin_amdgcn_sched_barrier(0);
         X[t] = fmaf(-e_at(t), X[t + 1], X[t]) * Wi[t];
         amax = fmaxf(amax, fabsf(X[t]));
       }
@@ -585,7 +613,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(B == 32 && k
     for (int k = 2; k < B; ++k) {
       const bool in = kCPL * c < 16 * (((k - 1) >> 4) + 1);  // inside the stored reflector
       const float* v = refl + refl_off(k) + (in ? kCPL * c : 0);
-      const float tau = in ? sTau[it][k] : 0.0f;
       float x[kCPL];
 #pragma unroll
       for (int m = 0; m < kCPL; m += 4) {
@@ -605,7 +632,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(B == 32 && k
       d += dpp_f<0xB1>(d);
       if (kLPV >= 4) d += dpp_f<0x4E>(d);
       if (kLPV >= 8) d += dpp_f<0x141>(d);
-      const float f = -tau * d;
+      const float f = in ? -d : 0.0f;
 #pragma unroll
       for (int m = 0; m < kCPL; ++m) y[m] = fmaf(f, x[m], y[m]);
     }
@@ -642,11 +669,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(B == 32 && k
       const bool uok = ur >= 0 && ur < kMaxR;
 #pragma unroll
       for (int s = 0; s < B / 4; ++s) {
+        if (s % 8 == 0) __builtin_amdgcn_sched_barrier(0);
         const float uv = uok ? U_at(t, 4 * s + q4, uok ? ur : 0) : 0.0f;
         float x[8];
 #pragma unroll
         for (int u = 0; u < 8 / kVec; ++u)
-          chunk_to_f<KT>(key16(t, 4 * s + q4, 8 * l16 + u * kVec), &x[u * kVec]);
+          chunk_to_f<KT>(key16(t, 4 * s, off_row + 16u * u), &x[u * kVec]);
 #pragma unroll
         for (int T = 0; T < 8; ++T)
           acc[T] = __builtin_amdgcn_mfma_f32_16x16x4f32(uv, x[T] - mu8[T], acc[T], 0, 0, 0);

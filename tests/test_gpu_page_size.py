@@ -286,3 +286,52 @@ def test_full_size_128k_large_pages(Bp):
         print(f"[page {Bp}] 128K unit ({s}, {h}): hat s err {err:.2e}, same table "
               f"{got == ref['ids']}, rel-L2 {w:.2e}", flush=True)
         assert err <= LSE_TOL
+
+
+@pytest.mark.parametrize("Bp,rank,kv", [(32, 8, "bf16"), (64, 8, "bf16"), (64, 11, "fp32"),
+                                        (32, 9, "bf16")])
+def test_build_of_degenerate_pages_and_odd_lists(Bp, rank, kv):
+    """Pages with zero, one, three and all modes, in counts that leave a wave half
+    empty: the reconstruction mu + V C^T against the oracle's, dropped modes exactly
+    zero, and a build list (odd, with pairs that name no page) that writes the same
+    records as the full build and nothing else."""
+    n = 7
+    d = _dev("degenerate", Bp, 1, 1, 1, [Bp * n + 3], rank, 256, kv, kv)
+    g = torch.Generator().manual_seed(5)
+    base = torch.randn(128, generator=g) * 3
+    blocks = d.w.page_table[0, :n].long()
+    k = d.w.k_cache
+    k[blocks[0], 0] = base.to(k.dtype)                                   # identical keys
+    k[blocks[1], 0] = base.to(k.dtype)
+    k[blocks[1], 0, Bp // 2:] = (base + torch.randn(128, generator=g)).to(k.dtype)
+    k[blocks[2], 0] = base.to(k.dtype)
+    k[blocks[2], 0, Bp - 1] = (base * 5).to(k.dtype)                     # one outlier token
+    t = torch.randn(Bp, 3, generator=g).round() @ (torch.randn(3, 128, generator=g) * 4).round()
+    k[blocks[3], 0] = t.to(k.dtype)                                      # rank 3
+    k[blocks[4], 0] = 0
+    d.k.copy_(k)
+    pages = [[0, j] for j in range(n)]
+    lst = torch.tensor(pages, dtype=torch.int32, device=d.device)
+    mu, V, C, s2 = (x.double().cpu().numpy()[:, 0] for x in
+                    B.build_factors(d.cfg, d.k, d.pt, d.sl, lst))
+    keys = k[blocks, 0].double().numpy()
+    f = O.build_factors(keys, rank)
+    got = mu[:, None] + np.einsum("pil,pcl->pic", C, V)
+    want = f["mu"][:, None] + np.einsum("pil,pcl->pic", f["C"], f["V"])
+    scale = np.sqrt((keys ** 2).sum(-1).max(-1))[:, None, None] + 1e-30
+    full = f["kept"] < rank                                               # no cut inside a spectrum
+    assert np.max(np.abs(got - want)[full] / scale[full]) <= 1e-5
+    for p in range(5):
+        kk = int(f["kept"][p])
+        assert np.all(V[p][:, kk:] == 0) and np.all(C[p][:, kk:] == 0), (p, kk)
+    store, part = B.alloc_summaries(d.cfg, d.device), B.alloc_summaries(d.cfg, d.device)
+    B.build_summaries(d.cfg, d.k, d.pt, d.sl, store)
+    some = torch.tensor([[0, 5], [0, n], [0, -1], [1, 0], [0, 3]], dtype=torch.int32, device=d.device)
+    B.build_summaries(d.cfg, d.k, d.pt, d.sl, part, build_list=some)
+    torch.cuda.synchronize()
+    for j in range(n):
+        b = int(blocks[j])
+        if j in (3, 5):
+            assert torch.equal(store[b], part[b])
+        else:
+            assert not part[b].any()
