@@ -216,7 +216,7 @@ __global__ __launch_bounds__(64) void build_kernel(
     ld_row(&sA[grp][li][0], a);
     __syncthreads();
     float lam, u[kMaxRank];
-    tri16::eig16<kFactors, kMaxRank>(a, li, r, lam, u, &sA[grp][0][0]);
+    tri16::eig16<kFactors, kMaxRank>(a, energy, li, r, lam, u, &sA[grp][0][0]);
     sLam[grp][li] = fmaxf(lam, 0.0f);
 #pragma unroll
     for (int l = 0; l < kMaxRank; ++l)

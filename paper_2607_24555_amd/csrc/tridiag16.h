@@ -81,18 +81,28 @@ __device__ __forceinline__ void static_for(F&& f) {
   for_each_int(f, std::make_integer_sequence<int, N>{});
 }
 
-// a: row i of A (consumed: holds the reflectors afterwards).  kAll: all 16
+// a: row i of A (consumed: holds the reflectors afterwards).  scale: the same bound of the
+// entries' magnitude, up to a factor of 16, in every lane of the row.  kAll: all 16
 // eigenvalues are wanted (else the r leading ones).  On return lam is the i-th
 // largest eigenvalue (for i < r, or every i with kAll) and u[l] (l < r) is
 // component i of the unit eigenvector of the l-th largest.  scratch: 16 x kXRow
 // floats of LDS owned by this row; the caller's wave runs this code without
 // divergence (every lane of the wave, DPP reads neighbouring lanes).
 template <bool kAll, int kMaxR>
-__device__ __forceinline__ void eig16(float (&a)[kN], const int i, const int r, float& lam,
-                                      float (&u)[kMaxR], float* scratch) {
+__device__ __forceinline__ void eig16(float (&a)[kN], const float scale, const int i, const int r,
+                                      float& lam, float (&u)[kMaxR], float* scratch) {
   float d[kN], e[kN], tau[kN - 2];
 
-  // ---- 1. Householder reduction
+  // ---- 0. scale by a power of two near 1 / scale
+  const int ex = scale > 0.0f && scale < INFINITY ? __builtin_amdgcn_frexp_expf(scale) : 0;
+#pragma unroll
+  for (int j = 0; j < kN; ++j) a[j] = __builtin_amdgcn_ldexpf(a[j], -ex);
+
+  // ---- 1. Householder reduction.  A column whose entries below the subdiagonal are
+  // below 2^-50 of `scale` counts as reduced: the rounding residue of a page of few
+  // modes shrinks step by step towards the denormals, where the hardware reciprocals
+  // overflow.
+  constexpr float kTinySq = 0x1p-100f;
   static_for<kN - 2>([&](auto kc) __attribute__((always_inline)) {
     constexpr int k = decltype(kc)::value;
     float x[kN];  // column k below the diagonal, from lane k's row
@@ -106,7 +116,7 @@ __device__ __forceinline__ void eig16(float (&a)[kN], const int i, const int r, 
     // (hardware square root and reciprocals: the reflector need only be
     // orthogonal to a few ulp, which its own tau guarantees)
     float t = 0.0f, v0 = 1.0f, beta = x0;
-    if (sig > 0.0f) {
+    if (sig > kTinySq) {
       const float mu = __builtin_amdgcn_sqrtf(fmaf(x0, x0, sig));
       v0 = x0 <= 0.0f ? x0 - mu : -sig * __builtin_amdgcn_rcpf(x0 + mu);
       t = 2.0f * v0 * v0 * __builtin_amdgcn_rcpf(fmaf(v0, v0, sig));
@@ -115,7 +125,7 @@ __device__ __forceinline__ void eig16(float (&a)[kN], const int i, const int r, 
     e[k] = beta;
     tau[k] = t;
     float v[kN];
-    const float iv0 = sig > 0.0f ? __builtin_amdgcn_rcpf(v0) : 0.0f;
+    const float iv0 = sig > kTinySq ? __builtin_amdgcn_rcpf(v0) : 0.0f;
     v[k + 1] = 1.0f;
 #pragma unroll
     for (int j = k + 2; j < kN; ++j) v[j] = x[j] * iv0;
@@ -290,6 +300,8 @@ __device__ __forceinline__ void eig16(float (&a)[kN], const int i, const int r, 
       __builtin_amdgcn_wave_barrier();
     }
   }
+
+  lam = __builtin_amdgcn_ldexpf(lam, ex);
 
   // ---- 4. back-transformation through the stored reflectors
   static_for<kN - 2>([&](auto kc) __attribute__((always_inline)) {

@@ -289,7 +289,8 @@ def test_full_size_128k_large_pages(Bp):
 
 
 @pytest.mark.parametrize("Bp,rank,kv", [(32, 8, "bf16"), (64, 8, "bf16"), (64, 11, "fp32"),
-                                        (32, 9, "bf16")])
+                                        (32, 9, "bf16"), (16, 8, "bf16"), (16, 15, "fp32"),
+                                        (16, 4, "bf16")])
 def test_build_of_degenerate_pages_and_odd_lists(Bp, rank, kv):
     """Pages with zero, one, three and all modes, in counts that leave a wave half
     empty: the reconstruction mu + V C^T against the oracle's, dropped modes exactly
