@@ -167,21 +167,27 @@ int sparse_splits(const locks_cfg_t& c) {
   return ((page_budget(c) << sub_page_log2(c)) + pps - 1) / pps;
 }
 
-// Dense baseline: pages per split block, 256 (64 per wave), halved while the grid
-// would hold fewer than 512 blocks -- two per compute unit -- so that short
-// contexts and small batches still fill the chip.
-int dense_pages_per_split(const locks_cfg_t& c) {
+// Dense attention: pages per split block, 256 (64 per wave), halved while the grid
+// would hold fewer than `blocks` blocks, so that short contexts and small batches still
+// fill the chip.
+int dense_pages_per_split(const locks_cfg_t& c, long blocks) {
   const long units = (long)c.num_seqs * c.num_kv_heads;
   const long span = (long)c.max_pages_per_seq << sub_page_log2(c);
   int pps = kDensePagesPerSplit;
-  while (pps > 4 && units * ((span + pps - 1) / pps) < 512) pps /= 2;
+  while (pps > 4 && units * ((span + pps - 1) / pps) < blocks) pps /= 2;
   return pps;
 }
 
-int dense_splits(const locks_cfg_t& c) {
-  const int pps = dense_pages_per_split(c);
+int dense_splits(const locks_cfg_t& c, int pps) {
   return (int)((((long)c.max_pages_per_seq << sub_page_log2(c)) + pps - 1) / pps);
 }
+
+// Blocks the workspace plan holds dense partials for, two per compute unit, and blocks
+// the launch asks for: with ragged lengths about half of the grid is past its sequence's
+// end, and four per compute unit balance the rest (8 sequences of 3K to 65K tokens, 8 KV
+// heads: 237 us at 512 blocks, 214 at 1,024, 216 at 2,048, 241 at 4,096, where the
+// per-block latency shows).
+constexpr long kDensePlanBlocks = 512, kDenseBlocks = 1024;
 
 // The build for the configuration's page size: the register-resident kernel of
 // build.hip for 16-token pages (which also serves a step's overlapped build), the
@@ -209,7 +215,8 @@ WsPlan plan_workspace(const locks_cfg_t& c) {
   const size_t K = k > 2 ? (size_t)(k - 2) : 1;
   p.n_chunks = (int)((mp + kSelChunk - 1) / kSelChunk);
   const int sp = ((k << sub_page_log2(c)) + kSparsePagesPerSplit - 1) / kSparsePagesPerSplit;
-  p.n_splits = sp > dense_splits(c) ? sp : dense_splits(c);
+  const int dsp = dense_splits(c, dense_pages_per_split(c, kDensePlanBlocks));
+  p.n_splits = sp > dsp ? sp : dsp;
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t o = off; off = align256(off + bytes); return o; };
   p.s_hat_off = take(S * Hq * mp * sizeof(float));
@@ -375,10 +382,15 @@ int locks_dense_attend(const locks_cfg_t* cfg, const void* q, const void* k_cach
   if (cfg->num_seqs == 0) return LOCKS_OK;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if ((rc = checked_tables(*cfg, ws, page_table, seq_lens, st))) return rc;
+  // the partials may take the whole workspace up to the checked tables; the plan's own
+  // split always fits
   const WsPlan p = plan_workspace(*cfg);
-  return hip_status(launch_attend(*cfg, q, k_cache, v_cache, page_table, seq_lens, nullptr,
-                                  dense_pages_per_split(*cfg), dense_splits(*cfg), carve(ws, p).attn, out,
-                                  out_lse, st));
+  const size_t row = (size_t)cfg->num_seqs * cfg->num_q_heads * (kDim + 2) * sizeof(float);
+  int pps = dense_pages_per_split(*cfg, kDenseBlocks);
+  while (pps < kDensePagesPerSplit && row * (size_t)dense_splits(*cfg, pps) > p.chk_pt_off) pps *= 2;
+  return hip_status(launch_attend(*cfg, q, k_cache, v_cache, page_table, seq_lens, nullptr, pps,
+                                  dense_splits(*cfg, pps), static_cast<float*>(ws), out, out_lse,
+                                  st));
 }
 
 int locks_kivi_quantize(const locks_cfg_t* cfg, const locks_kivi_t* kivi, void* k_cache,

@@ -338,3 +338,26 @@ def test_step_build_list_branches(name):
                                                         lse[s, hs].double().cpu().numpy()))
     print(f"[paths {name}] equals the separate calls bit for bit; rel-L2 on its tables "
           f"{worst:.2e}")
+
+
+@pytest.mark.parametrize("G,page", [(4, 16), (7, 16), (16, 64), (2, 32)])
+def test_dense_attention_of_ragged_batches(G, page):
+    """Dense attention where most blocks lie past their sequence's end: empty
+    sequences, single tokens, lengths on and around a wave's and a block's units."""
+    lens = [16 * 64, 0, 1, 16 * 64 + 1, 16 * 16 - 1, 7000, 16 * 256, 16 * 3 + 9]
+    spec = WorkloadSpec("dense", len(lens), 2 * G, 2, lens, 8, 16 * page, "bf16", "bf16",
+                        page_size=page)
+    d = Dev(build_workload(spec, 23))
+    out, lse = B.dense_attend(d.cfg, d.q, d.k, d.v, d.pt, d.sl, d.ws)
+    torch.cuda.synchronize()
+    for s in range(len(lens)):
+        for h in range(2):
+            k, v, qg = d.unit(s, h)
+            o, l = O.dense_step(qg, k, v)
+            hs = slice(h * G, (h + 1) * G)
+            got = out[s, hs].double().cpu().numpy()
+            if lens[s] == 0:
+                assert not got.any() and torch.isneginf(lse[s, hs]).all()
+                continue
+            assert max(rel_l2(got[g], o[g]) for g in range(G)) <= OUT_TOL
+            np.testing.assert_allclose(lse[s, hs].double().cpu().numpy(), l, atol=LSE_TOL)
