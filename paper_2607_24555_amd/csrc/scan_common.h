@@ -224,6 +224,112 @@ __device__ __forceinline__ QDigits q_digits(const QT* __restrict__ qrow, int grp
   return D;
 }
 
+// The digits of the block's HG head columns (heads past G repeat head 0), formed once per
+// block of 256 threads and read back by every wave: 16 threads per head, 8 elements each
+// (each wave forming all of its lanes' digits itself took about 300 VALU instructions, a
+// tenth to a sixth of the wave's work).  Thread seg of a head holds elements 8 seg .. + 7:
+// half of the 16 bytes that lane group seg / 4 uses in MFMA half (seg / 2) % 2.
+template <int HG>
+struct DigitLds {
+  i4v bd[3][2][4][HG];  // [digit][half][lane group][head]
+  int bias[3][HG];
+  float inv_scale[HG];
+};
+
+// (rows of a query tensor that starts off a 16-byte boundary are read element by element)
+template <typename QT>
+__device__ __forceinline__ bool load8_unaligned(const QT* p, float (&x)[8]) {
+  if (!(reinterpret_cast<uintptr_t>(p) & 15)) return false;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) x[e] = load_q(p, e);
+  return true;
+}
+__device__ __forceinline__ void load8_q(const uint16_t* p, float (&x)[8]) {
+  if (load8_unaligned(p, x)) return;
+  const uint4 w = *reinterpret_cast<const uint4*>(p);
+  const uint32_t u[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    x[2 * e] = __uint_as_float(u[e] << 16);
+    x[2 * e + 1] = __uint_as_float(u[e] & 0xffff0000u);
+  }
+}
+__device__ __forceinline__ void load8_q(const float* p, float (&x)[8]) {
+  if (load8_unaligned(p, x)) return;
+  const float4 a = reinterpret_cast<const float4*>(p)[0], b = reinterpret_cast<const float4*>(p)[1];
+  x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
+  x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+}
+template <int C>
+__device__ __forceinline__ int dpp_i(int v) {
+  return __builtin_amdgcn_mov_dpp(v, C, 0xF, 0xF, true);
+}
+
+// Called by all 256 threads (q: the group's first row); a barrier must follow before the
+// digits are read.
+template <typename QT, int HG>
+__device__ __forceinline__ void block_digits(const QT* __restrict__ q, int G, DigitLds<HG>& S) {
+  constexpr float c0 = 1.4426950408889634f * 0.08838834764831845f;  // log2(e) / sqrt(128)
+  const int hd = threadIdx.x >> 4, seg = threadIdx.x & 15;
+  if (hd >= HG) return;
+  float x[8];
+  load8_q(q + (hd < G ? hd : 0) * kDim + 8 * seg, x);
+  float m = 0.0f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(x[e]));
+  m = fmaxf(m, __int_as_float(dpp_i<0xB1>(__float_as_int(m))));
+  m = fmaxf(m, __int_as_float(dpp_i<0x4E>(__float_as_int(m))));
+  m = fmaxf(m, __int_as_float(dpp_i<0x141>(__float_as_int(m))));
+  m = fmaxf(m, __int_as_float(dpp_i<0x140>(__float_as_int(m))));
+  int ex = 0;
+  (void)frexpf(m, &ex);  // m < 2^ex
+  const float qscale = ldexpf(1.0f, 20 - ex);
+  uint32_t U[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int Q = m > 0.0f ? min(max((int)rintf(x[e] * qscale), -0xFFFFF), 0xFFFFF) : 0;
+    U[e] = (uint32_t)(Q + 0x808080);
+  }
+  uint32_t w[3][2];  // [digit][even, odd elements]
+#pragma unroll
+  for (int o = 0; o < 2; ++o) {
+    const uint32_t lo01 = __builtin_amdgcn_perm(U[o + 2], U[o], 0x05010400u);
+    const uint32_t lo23 = __builtin_amdgcn_perm(U[o + 6], U[o + 4], 0x05010400u);
+    const uint32_t hi01 = __builtin_amdgcn_perm(U[o + 2], U[o], 0x07030602u);
+    const uint32_t hi23 = __builtin_amdgcn_perm(U[o + 6], U[o + 4], 0x07030602u);
+    w[2][o] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u) ^ 0x80808080u;
+    w[1][o] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u) ^ 0x80808080u;
+    w[0][o] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u) ^ 0x80808080u;
+  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    *reinterpret_cast<uint2*>(reinterpret_cast<uint32_t*>(&S.bd[d][(seg >> 1) & 1][seg >> 2][hd]) +
+                              2 * (seg & 1)) = make_uint2(w[d][0], w[d][1]);
+    int b = __builtin_amdgcn_sdot4((int)w[d][0], 0x01010101, 0, false);
+    b = __builtin_amdgcn_sdot4((int)w[d][1], 0x01010101, b, false);
+    b += dpp_i<0xB1>(b);
+    b += dpp_i<0x4E>(b);
+    b += dpp_i<0x141>(b);
+    b += dpp_i<0x140>(b);
+    if (seg == 0) S.bias[d][hd] = -8 * b;
+  }
+  if (seg == 0) S.inv_scale[hd] = ldexpf(1.0f, ex - 20) * c0;
+}
+
+// Lane (grp, head)'s digits.
+template <int HG>
+__device__ __forceinline__ QDigits lane_digits(const DigitLds<HG>& S, int grp, int head) {
+  QDigits D;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    D.bd[d][0] = S.bd[d][0][grp][head];
+    D.bd[d][1] = S.bd[d][1][grp][head];
+    D.bias[d] = S.bias[d][head];
+  }
+  D.inv_scale = S.inv_scale[head];
+  return D;
+}
+
 // A 16-byte basis slice (32 excess-8 nibbles) as the int8 A operands of the two
 // K halves.
 __device__ __forceinline__ void nib_operands(const uint4& v, i4v (&a)[2]) {

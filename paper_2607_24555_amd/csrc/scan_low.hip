@@ -39,7 +39,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   __shared__ __align__(16) float sP[4][16][G][R];
   __shared__ float sA[4][16][G];
   __shared__ float2 sRun[4][64];
-  __shared__ __align__(16) i4v sQ[3][2][64];  // query digit operands, shared by the waves
+  __shared__ DigitLds<G> sDig;  // query digits, shared by the waves
 
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int col = lane & 15, grp = lane >> 4;
@@ -75,33 +75,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
       ld[u] = bld16(rs, rec_off(b, blk_bytes, head_off) + (c % kCh) * 16);
     }
   };
-  // the query digits (identical for the four waves) stay in LDS and are read at
-  // each use, leaving the registers to the loads in flight
-  int bias[3];
-  float inv_scale;
-  {
-    const QDigits QD = q_digits(q + (row0 + (col & 3)) * kDim, grp);
-    if (wave == 0) {
-#pragma unroll
-      for (int d = 0; d < 3; ++d)
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) sQ[d][hh][lane] = QD.bd[d][hh];
-    }
-#pragma unroll
-    for (int d = 0; d < 3; ++d) bias[d] = QD.bias[d];
-    inv_scale = QD.inv_scale;
-  }
+  // the query digits stay in LDS and are read at each use, leaving the registers to the
+  // loads in flight
+  block_digits<QT, G>(q + row0 * kDim, G, sDig);
   // the first step's records (the page-table load was in flight while the
   // digits were formed)
   uint4 ld[kLoads];
   if (has) issue(0, ld);
   __syncthreads();
+  int bias[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) bias[d] = sDig.bias[d][col & 3];
+  const float inv_scale = sDig.inv_scale[col & 3];
   // (the empty asm makes every use a fresh LDS read: hoisted out of the step loop
   // the operands would take 24 registers again)
   auto qop = [&](int d, int hh) {
-    int li = lane;
-    asm volatile("" : "+v"(li));
-    return sQ[d][hh][li];
+    int gi = grp;
+    asm volatile("" : "+v"(gi));
+    return sDig.bd[d][hh][gi][col & 3];
   };
 
   if (has) {

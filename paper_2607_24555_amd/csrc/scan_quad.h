@@ -76,6 +76,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
   constexpr uint32_t kStride = rec_stride(R, 0, P);
   constexpr uint32_t kCoef = rec_coef_off(R), kMu = rec_mu_off(R, 0, P), kSc = rec_scale_off(R, 0, P);
   __shared__ float2 sRun[4][16];
+  __shared__ DigitLds<HG> sDig;
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int col = lane & 15, grp = lane >> 4;
@@ -91,15 +92,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
 
   constexpr int kWavePages = 16 * kSteps;
   const int first = pg * kWavePages;
-  if (first < n_c) {
-    const int n_steps = min(kSteps, (n_c - first + 15) / 16);
-    // the query digits are formed once the first step's loads are in flight
-    QDigits QD;
+  if (scan_chunk() * 4 * kWavePages >= n_c) {  // no complete page in this block
+    if (threadIdx.x < G)
+      partials[(row0 + threadIdx.x) * gridDim.x + blockIdx.x] = make_float2(-INFINITY, 0.0f);
+    return;
+  }
+  const bool has = first < n_c;  // pages for this wave
+  {
+    const int n_steps = has ? min(kSteps, (n_c - first + 15) / 16) : 0;
+    QDigits QD;          // read from the block's once formed
     float inv_m = 0.0f;  // scale of the stage-1 values; zero where the page is not the column's
-    auto form_digits = [&]() {
-      QD = q_digits(q + (row0 + (g < G ? g : 0)) * kDim, grp);
-      inv_m = mine ? QD.inv_scale : 0.0f;
-    };
     // own(u): the u-th page of the step (0 .. 15) whose score this lane finishes
     auto own = [&](int u) { return HG == 4 ? 4 * grp + cb : 4 * grp + 2 * u + cb; };
     float* shat_lane = s_hat + lay.base(s, h) + (long)g * lay.head;
@@ -388,14 +390,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
         run(first + 16 * t, IntTag<1>{}, safe_tag, 0);
       }
     };
+    // with several steps a wave, the first step's records are on their way while the
+    // digits are formed (1M decode steps: 53.7 us, 55.3 the other way round); with one, in
+    // grids that leave most of the chip idle, holding those registers across the barrier
+    // costs more than it hides (32K decode steps: 26.2 us against 26.8)
+    int blk0 = 0, blk1 = 0;
     if (n_steps == kSteps) {
-      const int blk0 = lane_block_clamped<V>(pt_row, first, n_c, lane);
-      const int blk1 = kSteps > 1 ? lane_block_clamped<V>(pt_row, first + 16, n_c, lane) : 0;
-      load_step(blk0);
-      form_digits();
+      blk0 = lane_block_clamped<V>(pt_row, first, n_c, lane);
+      blk1 = kSteps > 1 ? lane_block_clamped<V>(pt_row, first + 16, n_c, lane) : 0;
+      if (kSteps > 1) load_step(blk0);
+    }
+    block_digits<QT, HG>(q + row0 * kDim, G, sDig);
+    __syncthreads();
+    QD = lane_digits(sDig, grp, g);
+    inv_m = mine ? QD.inv_scale : 0.0f;
+    if (n_steps == kSteps) {
+      if (kSteps == 1) load_step(blk0);
       run(first, IntTag<kSteps>{}, IntTag<0>{}, blk1);
     } else {
-      form_digits();
       run_each(IntTag<0>{});
     }
     if (__any(bad)) {

@@ -178,6 +178,19 @@ def test_rank8_scan_of_widely_spread_logits(G, page):
     _rank8_against_oracle(d, page, {(s, h) for s in (0, 1) for h in (0, 1)}, rtol=2e-6)
 
 
+@pytest.mark.parametrize("G,rank,q", [(4, 8, "bf16"), (16, 8, "fp32"), (4, 2, "bf16")])
+def test_scores_with_an_unaligned_query(G, rank, q):
+    """A query tensor that starts one element past a 16-byte boundary scores the same bits."""
+    d = _dev("unaligned", 1, G, 2, [16 * 90 + 3], rank, 256, "bf16", q)
+    store, _ = d.oracle_summaries()
+    want = B.score_pages(d.cfg, d.q, store, d.pt, d.sl, d.ws)
+    buf = torch.empty(d.q.numel() + 1, dtype=d.q.dtype, device=d.device)
+    buf[1:] = d.q.flatten()
+    got = B.score_pages(d.cfg, buf[1:].view(d.q.shape), store, d.pt, d.sl, d.ws)
+    torch.cuda.synchronize()
+    assert torch.equal(got[..., :90], want[..., :90])
+
+
 STEP_CASES = {
     # name: (G, rank, kv dtype, q dtype)
     "G16-r2": (16, 2, "bf16", "bf16"),
