@@ -220,7 +220,6 @@ WsPlan plan_workspace(const locks_cfg_t& c) {
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t o = off; off = align256(off + bytes); return o; };
   p.s_hat_off = take(S * Hq * mp * sizeof(float));
-  p.part_off = take(S * Hq * (size_t)scan_blocks(c) * sizeof(float2));
   // survivor rows: the block-level path keeps k - 2 per chunk, the fast path `width`
   const size_t rows = (size_t)select_fast_rows(c);
   size_t surv = (size_t)p.n_chunks * K;
@@ -230,7 +229,11 @@ WsPlan plan_workspace(const locks_cfg_t& c) {
   p.cblk_off = take(S * Hkv * surv * sizeof(int32_t));
   p.sat_off = take(S * Hkv * rows * sizeof(uint32_t));
   p.keys_off = take(S * Hkv * mp * sizeof(uint32_t));
-  p.attn_off = take(S * Hq * (size_t)p.n_splits * (kDim + 2) * sizeof(float));
+  // the scan's partials lie where the attention's do: the selection has read them before
+  // the attention writes
+  const size_t attn = S * Hq * (size_t)p.n_splits * (kDim + 2) * sizeof(float);
+  const size_t part = S * Hq * (size_t)scan_blocks(c) * sizeof(float2);
+  p.attn_off = p.part_off = take(attn > part ? attn : part);
   p.slscan_off = take(S * sizeof(int32_t));
   p.partx_off = take(S * Hq * sizeof(float2));
   p.chk_pt_off = take(S * mp * sizeof(int32_t));

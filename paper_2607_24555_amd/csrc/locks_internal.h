@@ -91,7 +91,7 @@ inline SHatLayout shat_head_minor(const locks_cfg_t& c) {
 
 struct WsPlan {
   size_t s_hat_off;   // float [S][H_kv][max_pages][G]    page scores (head-minor)
-  size_t part_off;    // float2 [S][H_q][scan blocks]     (max, sum exp), log2 domain
+  size_t part_off;    // float2 [S][H_q][scan blocks]     (max, sum exp), log2 domain; = attn_off
   size_t ckey_off;    // uint32 [S][H_kv][rows][width]    per-chunk survivors (keys)
   size_t cidx_off;    // int32  [S][H_kv][rows][width]    per-chunk survivors (pages)
   size_t cblk_off;    // int32  [S][H_kv][rows][width]    per-chunk survivors (physical blocks)
