@@ -212,7 +212,6 @@ WsPlan plan_workspace(const locks_cfg_t& c) {
   const size_t S = (size_t)c.num_seqs, Hq = (size_t)c.num_q_heads, Hkv = (size_t)c.num_kv_heads;
   const size_t mp = (size_t)c.max_pages_per_seq;
   const int k = page_budget(c);
-  const size_t K = k > 2 ? (size_t)(k - 2) : 1;
   p.n_chunks = (int)((mp + kSelChunk - 1) / kSelChunk);
   const int sp = ((k << sub_page_log2(c)) + kSparsePagesPerSplit - 1) / kSparsePagesPerSplit;
   const int dsp = dense_splits(c, dense_pages_per_split(c, kDensePlanBlocks));
@@ -222,8 +221,7 @@ WsPlan plan_workspace(const locks_cfg_t& c) {
   p.s_hat_off = take(S * Hq * mp * sizeof(float));
   // survivor rows: the block-level path keeps k - 2 per chunk, the fast path `width`
   const size_t rows = (size_t)select_fast_rows(c);
-  size_t surv = (size_t)p.n_chunks * K;
-  if (rows * (size_t)select_fast_width(c) > surv) surv = rows * (size_t)select_fast_width(c);
+  const size_t surv = (size_t)select_survivors(c);
   p.ckey_off = take(S * Hkv * surv * sizeof(uint32_t));
   p.cidx_off = take(S * Hkv * surv * sizeof(int32_t));
   p.cblk_off = take(S * Hkv * surv * sizeof(int32_t));

@@ -184,7 +184,7 @@ __device__ __forceinline__ void load_page(PageRegs& P, const uint16_t* kp, const
 // Chunk survivors and outputs of the selection merged into the attention kernel.
 struct SelTable {
   SelectBufs sb;
-  int n_rows, width;
+  int n_rows, width, chunk;
   const float* s_hat;
   SHatLayout lay;
   int32_t* out_ids;
@@ -197,7 +197,8 @@ struct SelTable {
 // (dense attention of 8 ragged sequences, 1.1 GB of K and V: 272 us with a lookup per
 // unit and 64 stand-in loads in every block past its sequence's end, 214 us now, 5.2
 // TB/s, the rate of a plain copy).
-template <bool kSelect, int kPPW>
+// kNK: survivors per lane of the selection merge (64 kNK per wave).
+template <bool kSelect, int kPPW, int kNK>
 __global__ __launch_bounds__(256) void attend_mfma_kernel(
     int H_q, int H_kv, int max_pages, int k_list, int pgsz, int lg_sub,
     const uint16_t* __restrict__ q,
@@ -214,11 +215,11 @@ __global__ __launch_bounds__(256) void attend_mfma_kernel(
   const int c16 = lane & 15, r4 = lane >> 4;
   const int G = H_q / H_kv;
   // the selection survivors are requested before the sequence length is known
-  UnionRegs<kUnionNK> UR;
+  UnionRegs<kNK> UR;
   if constexpr (kSelect) {
     const long unit = (long)s * H_kv + h;
     const long rb = unit * tb.n_rows * tb.width;
-    union_load<kUnionNK, 4>(UR, tb.n_rows, tb.width, tb.sb.cand_key + rb, tb.sb.cand_idx + rb,
+    union_load<kNK, 4>(UR, tb.n_rows, tb.width, tb.sb.cand_key + rb, tb.sb.cand_idx + rb,
                             tb.sb.cand_blk + rb, tb.sb.sat + unit * tb.n_rows);
   }
   const int L = seq_lens[s];
@@ -247,8 +248,8 @@ __global__ __launch_bounds__(256) void attend_mfma_kernel(
   const int32_t* ids = page_ids ? page_ids + ((long)s * H_kv + h) * k_list : nullptr;
   if constexpr (kSelect) {
     const long unit = (long)s * H_kv + h;
-    const int used = n > k_list ? (n - 2) / kFastChunk + 1 : 0;
-    union_table_from<kUnionNK, 4>(UR, k_list, n, used, tb.width, tb.sb.keys + unit * max_pages,
+    const int used = n > k_list ? (n - 2) / tb.chunk + 1 : 0;
+    union_table_from<kNK, 4>(UR, k_list, n, used, tb.width, tb.sb.keys + unit * max_pages,
                                   page_table + (long)s * max_pages, s_tab, s_blk, unionL);
     ids = s_tab;
   }
@@ -498,8 +499,14 @@ void launch_mfma(const locks_cfg_t& c, dim3 grid, hipStream_t st, const uint16_t
                  const int32_t* seq_lens, const int32_t* page_ids, int pages_per_split,
                  int n_splits, float* partial, SelTable tb) {
   const int ppw = pages_per_split % 4 == 0 ? pages_per_split / 4 : 0;
-#define LOCKS_ATTEND_MFMA(P)                                                                   \
-  hipLaunchKernelGGL((attend_mfma_kernel<kSelect, P>), grid, dim3(256), 0, st, c.num_q_heads,   \
+  // survivors held per lane: 2, 4 or the cap's 8
+  const int held = kSelect ? tb.n_rows * tb.width : 0;
+#define LOCKS_ATTEND_MFMA(P)                              \
+  if (held <= 2 * 256) LOCKS_ATTEND_MFMA_N(P, 2);        \
+  else if (held <= 4 * 256) LOCKS_ATTEND_MFMA_N(P, 4);   \
+  else LOCKS_ATTEND_MFMA_N(P, kUnionNK)
+#define LOCKS_ATTEND_MFMA_N(P, NK)                                                             \
+  hipLaunchKernelGGL((attend_mfma_kernel<kSelect, P, NK>), grid, dim3(256), 0, st, c.num_q_heads, \
                      c.num_kv_heads, c.max_pages_per_seq, page_budget(c), c.page_size,          \
                      sub_page_log2(c), q, k_cache, v_cache, page_table, seq_lens, page_ids,     \
                      pages_per_split, n_splits, partial, tb)
@@ -510,6 +517,7 @@ void launch_mfma(const locks_cfg_t& c, dim3 grid, hipStream_t st, const uint16_t
     case 8: LOCKS_ATTEND_MFMA(8); break;
     default: LOCKS_ATTEND_MFMA(0); break;
   }
+#undef LOCKS_ATTEND_MFMA_N
 #undef LOCKS_ATTEND_MFMA
 }
 
@@ -549,7 +557,8 @@ hipError_t launch_attend_select(const locks_cfg_t& c, const void* q, const void*
                                 SHatLayout lay, int32_t* out_ids, float* out_sel_lse,
                                 int pages_per_split, int n_splits, float* partial, float* out,
                                 float* out_lse, hipStream_t st) {
-  const SelTable tb{sb, select_fast_rows(c), select_fast_width(c), s_hat, lay, out_ids, out_sel_lse};
+  const SelTable tb{sb, select_rows(c), select_width(c), select_chunk_pages(c), s_hat, lay, out_ids,
+                    out_sel_lse};
   launch_mfma<true>(c, dim3(n_splits, c.num_kv_heads, c.num_seqs), st,
                     static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k_cache),
                     static_cast<const uint16_t*>(v_cache), page_table, seq_lens, nullptr,

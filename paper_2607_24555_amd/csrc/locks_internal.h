@@ -110,7 +110,7 @@ struct WsPlan {
 
 constexpr int kScanPagesPerBlock = 256;  // 4 waves x 64 pages (generic scan kernels)
 constexpr int kSelChunk = 1024;          // pages per selection chunk (block-level path)
-constexpr int kFastChunk = 512;          // pages per selection chunk (fast path)
+constexpr int kFastChunk = 512;          // smallest pages per selection chunk (fast path)
 constexpr int kUnionCap = 2048;          // chunk survivors one table merge holds
 constexpr int kUnionNK = kUnionCap / 256; // ... per lane of a 4-wave block
 constexpr int kSparsePagesPerSplit = 4;   // one page per wave of a 4-wave block
@@ -185,6 +185,12 @@ struct SelectBufs {
 bool select_fast_path(const locks_cfg_t& c);
 int select_fast_rows(const locks_cfg_t& c);
 int select_fast_width(const locks_cfg_t& c);
+// Pages per chunk and chunks per sequence of the launch (at most select_fast_rows).
+int select_chunk_pages(const locks_cfg_t& c);
+int select_rows(const locks_cfg_t& c);
+int select_width(const locks_cfg_t& c);
+// Survivors per (sequence, KV head) the workspace plan holds (both paths).
+long select_survivors(const locks_cfg_t& c);
 // Fast path, first half: every page's key and each chunk's top keys (in sb).
 // part_x (nullable): one more (max, sum) partial per query head, [S][H_q], valid
 // for the sequences with sl_scan[s] < seq_lens[s].

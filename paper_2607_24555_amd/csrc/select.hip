@@ -340,7 +340,7 @@ __global__ __launch_bounds__(kSelThreads) void select_merge_kernel(
 // ---------------------------------------------------------------------------
 // Fast path (k - 2 <= kFastK, at most kUnionCap / 8 chunks of kFastChunk pages).
 // Two kernels:
-//   chunk - one 4-wave block per kFastChunk pages of a (sequence, KV head): Z_g
+//   chunk - one 4-wave block per 512, 1,024 or 2,048 pages of a (sequence, KV head): Z_g
 //           from the scan partials, the share-averaged key of every page
 //           (also written out in full), and the
 //           chunk's top `width` keys with their pages and physical blocks, by a
@@ -356,7 +356,6 @@ __global__ __launch_bounds__(kSelThreads) void select_merge_kernel(
 
 constexpr int kChunkThreads = 256;
 constexpr int kChunkWaves = kChunkThreads / 64;
-constexpr int kChunkNK = kFastChunk / kChunkThreads;  // keys per lane in a chunk (2)
 
 // xor-shuffle inside groups of four lanes (DPP quad permutation).
 template <int O>
@@ -368,16 +367,18 @@ __device__ __forceinline__ uint32_t page_key(float m, float sum) {
   return max(1u, f32_order_key(m + __builtin_amdgcn_logf(sum)));
 }
 
-template <int kG>  // G when one page's G scores are contiguous (4, 8, 16), else 0
+// kG: G when one page's G scores are contiguous (4, 8, 16), else 0; kChunkNK keys per
+// lane: the chunk holds 256 kChunkNK pages
+template <int kG, int kChunkNK>
 __global__ __launch_bounds__(kChunkThreads) void select_chunk_keys_kernel(
     int H_q, int H_kv, int k, int width, int max_pages, int pgsz,
     const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ page_table,
     const float* __restrict__ s_hat, SHatLayout lay, const float2* __restrict__ partials,
     int n_parts, SelectBufs sb, int n_rows, const float2* __restrict__ part_x,
     const int32_t* __restrict__ sl_scan) {
-  constexpr int kT = kChunkThreads;
+  constexpr int kT = kChunkThreads, kChunk = kT * kChunkNK;
   __shared__ float s_lz2[kMaxGroup];
-  __shared__ __align__(16) uint32_t sk[kFastChunk];
+  __shared__ __align__(16) uint32_t sk[kChunk];
   __shared__ CutLds<kChunkWaves> L;
   __shared__ HistLds<kChunkWaves> HL;
   const int chunk = blockIdx.x, h = blockIdx.y, s = blockIdx.z, tid = threadIdx.x;
@@ -385,7 +386,7 @@ __global__ __launch_bounds__(kChunkThreads) void select_chunk_keys_kernel(
   const int Ls = seq_lens[s];  // used after the loads below are issued
   const int G = H_q / H_kv;
   const int K = k - 2;
-  const int p0 = chunk * kFastChunk;
+  const int p0 = chunk * kChunk;
   if (K <= 0) return;
   const long unit = (long)s * H_kv + h;
   const long row0 = (long)s * H_q + (long)h * G;
@@ -396,7 +397,7 @@ __global__ __launch_bounds__(kChunkThreads) void select_chunk_keys_kernel(
   // contiguous layout: float4 number f = kT i + tid of the chunk's span holds
   // heads 4 (f % LP) .. +3 of page p0 + f / LP; the LP lanes of a page are
   // adjacent.  These loads are issued before Z_g is reduced.
-  constexpr int LP = kG ? kG / 4 : 1, per = kG ? kFastChunk * kG / 4 / kT : 1;
+  constexpr int LP = kG ? kG / 4 : 1, per = kG ? kChunk * kG / 4 / kT : 1;
   float4 v[per];
   if constexpr (kG != 0) {
 #pragma unroll
@@ -483,7 +484,7 @@ __global__ __launch_bounds__(kChunkThreads) void select_chunk_keys_kernel(
 #pragma unroll
     for (int g = 0; g < kMaxGroup; ++g) lz[g] = g < G ? s_lz2[g] : 0.0f;
 #pragma unroll
-    for (int part = 0; part < kFastChunk / kT; ++part) {
+    for (int part = 0; part < kChunk / kT; ++part) {
       const int j = p0 + part * kT + tid;
       const long jj = min(max(j, 1), n - 2);
       float sv[kMaxGroup];
@@ -528,7 +529,7 @@ __global__ __launch_bounds__(kChunkThreads) void select_chunk_keys_kernel(
 }
 
 __global__ __launch_bounds__(kChunkThreads) void select_merge_fast_kernel(
-    int H_q, int H_kv, int k, int width, int n_rows, int max_pages, int pgsz,
+    int H_q, int H_kv, int k, int width, int n_rows, int chunk, int max_pages, int pgsz,
     const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ page_table,
     const float* __restrict__ s_hat, SHatLayout lay, SelectBufs sb, int32_t* __restrict__ out_ids,
     float* __restrict__ out_sel_lse) {
@@ -541,7 +542,7 @@ __global__ __launch_bounds__(kChunkThreads) void select_merge_fast_kernel(
   const int G = H_q / H_kv;
   const long row0 = (long)s * H_q + (long)h * G;
   const long unit = (long)s * H_kv + h;
-  const int used = n > k ? (n - 2) / kFastChunk + 1 : 0;
+  const int used = n > k ? (n - 2) / chunk + 1 : 0;
   union_table<kUnionNK, kChunkWaves>(
       k, n, used, width, sb.cand_key + unit * n_rows * width, sb.cand_idx + unit * n_rows * width,
       sb.cand_blk + unit * n_rows * width, sb.sat + unit * n_rows, sb.keys + unit * max_pages,
@@ -573,6 +574,42 @@ int select_fast_rows(const locks_cfg_t& c) {
   return (c.max_pages_per_seq + kFastChunk - 1) / kFastChunk;
 }
 
+// Pages per chunk of the launched grid: 512, or 1,024 / 2,048 where 512 would take more
+// blocks than the chip holds at once (eight per compute unit): a block's time is the
+// latency of its loads and barriers whatever its chunk, so the step of a batch of 64
+// sequences of up to 64K tokens x 8 KV heads took 171 us with 4,608 blocks, 168.4 with
+// 2,560 and 167.5 with 1,536.  In smaller grids larger chunks only lengthen the blocks (1M:
+// 53.8 us at 512, 54.9 at 1,024, 58.6 at 2,048).
+int select_chunk_pages(const locks_cfg_t& c) {
+  const long units = (long)c.num_kv_heads * c.num_seqs;
+  int chunk = kFastChunk;
+  while (chunk < 4 * kFastChunk && units * ((c.max_pages_per_seq + chunk - 1) / chunk) > 2048) chunk *= 2;
+  return chunk;
+}
+
+// Survivors kept per chunk of the launch: select_fast_width's rule on the launch's rows,
+// within the survivors that the workspace plan holds.
+int select_width(const locks_cfg_t& c) {
+  if (select_chunk_pages(c) == kFastChunk) return select_fast_width(c);
+  const int K = page_budget(c) - 2;
+  const long rows = select_rows(c), cap = select_survivors(c) < kUnionCap ? select_survivors(c) : kUnionCap;
+  int w = 8;
+  while (w < K && 2L * w * rows <= cap) w *= 2;
+  return w;
+}
+
+long select_survivors(const locks_cfg_t& c) {
+  const int k = page_budget(c);
+  const long chunks = (c.max_pages_per_seq + kSelChunk - 1) / kSelChunk, K = k > 2 ? k - 2 : 1;
+  const long fast = (long)select_fast_rows(c) * select_fast_width(c);
+  return chunks * K > fast ? chunks * K : fast;
+}
+
+int select_rows(const locks_cfg_t& c) {
+  const int chunk = select_chunk_pages(c);
+  return (c.max_pages_per_seq + chunk - 1) / chunk;
+}
+
 // Survivors kept per chunk: the smallest power of two >= k - 2, or fewer so
 // that all chunks' survivors fit one merge (at least 8).
 int select_fast_width(const locks_cfg_t& c) {
@@ -595,15 +632,24 @@ hipError_t launch_select_chunks(const locks_cfg_t& c, const int32_t* page_table,
   const int k = page_budget(c);
   const int G = c.num_q_heads / c.num_kv_heads;
   const bool contiguous = lay.head == 1 && lay.page == G;
-  auto* kern = select_chunk_keys_kernel<0>;
-  if (contiguous && G == 16) kern = select_chunk_keys_kernel<16>;
-  if (contiguous && G == 8) kern = select_chunk_keys_kernel<8>;
-  if (contiguous && G == 4) kern = select_chunk_keys_kernel<4>;
-  const int rows = select_fast_rows(c);
-  hipLaunchKernelGGL(kern, dim3(rows, c.num_kv_heads, c.num_seqs), dim3(kChunkThreads), 0, st,
-                     c.num_q_heads, c.num_kv_heads, k, select_fast_width(c), c.max_pages_per_seq,
-                     c.page_size, seq_lens, page_table, s_hat, lay, partials, scan_blocks(c), sb,
-                     rows, part_x, sl_scan);
+  const int rows = select_rows(c);
+#define LOCKS_CHUNK_KEYS(GG, NK)                                                              \
+  hipLaunchKernelGGL((select_chunk_keys_kernel<GG, NK>), dim3(rows, c.num_kv_heads, c.num_seqs), \
+                     dim3(kChunkThreads), 0, st, c.num_q_heads, c.num_kv_heads, k,            \
+                     select_width(c), c.max_pages_per_seq, c.page_size, seq_lens,        \
+                     page_table, s_hat, lay, partials, scan_blocks(c), sb, rows, part_x, sl_scan)
+#define LOCKS_CHUNK_KEYS_G(NK)                                \
+  if (contiguous && G == 16) LOCKS_CHUNK_KEYS(16, NK);        \
+  else if (contiguous && G == 8) LOCKS_CHUNK_KEYS(8, NK);     \
+  else if (contiguous && G == 4) LOCKS_CHUNK_KEYS(4, NK);     \
+  else LOCKS_CHUNK_KEYS(0, NK)
+  switch (select_chunk_pages(c) / kChunkThreads) {
+    case 2: LOCKS_CHUNK_KEYS_G(2); break;
+    case 4: LOCKS_CHUNK_KEYS_G(4); break;
+    default: LOCKS_CHUNK_KEYS_G(8); break;
+  }
+#undef LOCKS_CHUNK_KEYS_G
+#undef LOCKS_CHUNK_KEYS
   return hipGetLastError();
 }
 
@@ -617,8 +663,8 @@ hipError_t launch_select(const locks_cfg_t& c, const int32_t* page_table, const 
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(select_merge_fast_kernel, dim3(c.num_kv_heads, c.num_seqs),
                        dim3(kChunkThreads), 0, st, c.num_q_heads, c.num_kv_heads, k,
-                       select_fast_width(c), select_fast_rows(c), c.max_pages_per_seq, c.page_size,
-                       seq_lens, page_table, s_hat, lay, sb, out_page_ids, out_sel_lse);
+                       select_width(c), select_rows(c), select_chunk_pages(c), c.max_pages_per_seq,
+                       c.page_size, seq_lens, page_table, s_hat, lay, sb, out_page_ids, out_sel_lse);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(select_chunk_kernel, dim3(sb.n_chunks, c.num_kv_heads, c.num_seqs),

@@ -374,3 +374,25 @@ def test_dense_attention_of_ragged_batches(G, page):
                 continue
             assert max(rel_l2(got[g], o[g]) for g in range(G)) <= OUT_TOL
             np.testing.assert_allclose(lse[s, hs].double().cpu().numpy(), l, atol=LSE_TOL)
+
+
+@pytest.mark.parametrize("G,copies", [(4, 1), (4, 86), (2, 86), (4, 172), (16, 172)])
+def test_selection_chunk_sizes(G, copies):
+    """Selection in chunks of 512, 1,024 and 2,048 pages (the size grows with the
+    batch): three sequences that end just past a chunk, inside one and below the budget,
+    repeated until the grid takes the size.  The first copy is held to the oracle, the
+    others equal it."""
+    d = _dev("chunks", 3, G, 2, [16 * 2050 + 5, 16 * 1025 + 1, 16 * 40], 8, 2048, "bf16", "bf16")
+    store, recs = d.oracle_summaries()
+    refs, _ = _scores_against_oracle(d, store, recs)
+    d.cfg.num_seqs = 3 * copies
+    d.q, d.pt, d.sl = d.q.repeat(copies, 1, 1), d.pt.repeat(copies, 1), d.sl.repeat(copies)
+    d.ws = B.alloc_workspace(d.cfg, d.device)
+    ids, sel, out, lse = B.decode_step(d.cfg, d.q, d.k, d.v, d.pt, d.sl, store, d.ws)
+    ids2, sel2 = B.select(d.cfg, d.q, store, d.pt, d.sl, d.ws)
+    torch.cuda.synchronize()
+    assert torch.equal(ids, ids2)
+    for t in (ids, sel, out, lse):
+        c = t.view(torch.int32).view(copies, 3, *t.shape[1:])  # bits: open pages' scores are NaN
+        assert torch.equal(c, c[:1].expand_as(c))
+    _step_against_oracle(d, refs, ids, sel, out, lse)
