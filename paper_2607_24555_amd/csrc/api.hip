@@ -154,16 +154,22 @@ int check_ws(const locks_cfg_t* c, void* ws, size_t ws_bytes) {
 // grid would exceed ~512 blocks, so large batches stream several pages per
 // wave instead of paying per-block latency many times over.
 // (Counted in 16-token units: a table entry of B tokens is B / 16 of them.)
-int sparse_pages_per_split(const locks_cfg_t& c) {
+// The vector-ALU kernel (fp32 queries or caches) takes a block per unit, doubled in the
+// same way, where the workspace holds that many partials: its blocks have one unit in
+// flight at a time.
+int sparse_pages_per_split(const locks_cfg_t& c, int plan_splits) {
   const long units = (long)c.num_seqs * c.num_kv_heads;
   const int k = page_budget(c) << sub_page_log2(c);
   int pps = kSparsePagesPerSplit;
+  if (c.q_dtype != LOCKS_BF16 || c.kv_dtype != LOCKS_BF16) {
+    pps = 1;
+    while (pps < kSparsePagesPerSplit && (k + pps - 1) / pps > plan_splits) pps *= 2;
+  }
   while (pps < 32 && units * ((k + pps - 1) / pps) > 512) pps *= 2;
   return pps;
 }
 
-int sparse_splits(const locks_cfg_t& c) {
-  const int pps = sparse_pages_per_split(c);
+int sparse_splits(const locks_cfg_t& c, int pps) {
   return ((page_budget(c) << sub_page_log2(c)) + pps - 1) / pps;
 }
 
@@ -367,8 +373,8 @@ int locks_sparse_attend(const locks_cfg_t* cfg, const void* q, const void* k_cac
   hipStream_t st = static_cast<hipStream_t>(stream);
   if ((rc = checked_tables(*cfg, ws, page_table, seq_lens, st))) return rc;
   const WsPlan p = plan_workspace(*cfg);
-  const int pps = sparse_pages_per_split(*cfg);
-  const int splits = sparse_splits(*cfg);
+  const int pps = sparse_pages_per_split(*cfg, p.n_splits);
+  const int splits = sparse_splits(*cfg, pps);
   return hip_status(launch_attend(*cfg, q, k_cache, v_cache, page_table, seq_lens, page_ids,
                                   pps, splits, carve(ws, p).attn, out, out_lse, st));
 }
@@ -474,8 +480,8 @@ static int decode_step_impl(const locks_cfg_t* cfg, const locks_step_opts_t* opt
   auto post_kivi = [&]() -> int { return hip_status(kivi_at(LOCKS_KIVI_POST, st, kKiviAny)); };
   const WsPlan p = plan_workspace(*cfg);
   const Ws w = carve(ws, p);
-  const int pps = sparse_pages_per_split(*cfg);
-  const int splits = sparse_splits(*cfg);
+  const int pps = sparse_pages_per_split(*cfg, p.n_splits);
+  const int splits = sparse_splits(*cfg, pps);
   if (attend_select_fused(*cfg)) {
     // scan -> per-chunk selection -> attention whose blocks merge the table
     const SHatLayout lay = shat_head_minor(*cfg);

@@ -26,40 +26,83 @@ namespace {
 
 constexpr int kAttnBlock = 256;
 
-template <typename T>
-__device__ __forceinline__ float ld(const T* p, size_t i) { return load_elem(p, i); }
+// Eight consecutive elements as floats (16-byte loads where the tensor is so aligned).
+__device__ __forceinline__ void load8(const uint16_t* p, bool aligned, float (&x)[8]) {
+  if (aligned) {
+    const uint4 w = *reinterpret_cast<const uint4*>(p);
+    const uint32_t u[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      x[2 * e] = __uint_as_float(u[e] << 16);
+      x[2 * e + 1] = __uint_as_float(u[e] & 0xffff0000u);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = load_elem(p, e);
+  }
+}
+__device__ __forceinline__ void load8(const float* p, bool aligned, float (&x)[8]) {
+  if (aligned) {
+    const float4 a = reinterpret_cast<const float4*>(p)[0], b = reinterpret_cast<const float4*>(p)[1];
+    x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
+    x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = p[e];
+  }
+}
+// sum over a 16-lane row
+__device__ __forceinline__ float row16_sum(float v) {
+  v += __int_as_float(dpp<0xB1>(__float_as_int(v)));
+  v += __int_as_float(dpp<0x4E>(__float_as_int(v)));
+  v += __int_as_float(dpp<0x141>(__float_as_int(v)));
+  v += __int_as_float(dpp<0x140>(__float_as_int(v)));
+  return v;
+}
 
 // Work is counted in 16-token sub-pages: unit t of the list is sub-page t % nsub
 // of list entry t / nsub (nsub = B / 16 for pages of B tokens).
-template <typename QT, typename KT>
+//
+// Vector-ALU attention (fp32 queries or caches).  The block's 16 sixteen-lane rows take
+// one token of a unit each, lane seg of a row dims 8 seg .. + 7; every row runs its own
+// online softmax for the group's heads over its token slots, so the loop has no barrier
+// and no LDS, and the 16 rows are combined per head at the end.
+// A block holds kHeads heads (1 or 4); the further heads of a larger group are other
+// blocks, n_splits apart in the grid, which read the same pages from the cache.
+// Against four barriers and serial 128-term dot products per unit (sparse call and dense
+// call, us): one head, 16 pages of 256: 13.9 -> 6.3 and 16.0 -> 9.8; 8 sequences x 8 KV
+// heads x 4 heads, 128 pages of 1,024: 58.3 -> 30.5 and 293 -> 192 (5.6 TB/s); 16 heads
+// on 2 KV heads: 29.8 -> 29.9 and 162 -> 109.
+template <typename QT, typename KT, int kHeads>
 __global__ __launch_bounds__(kAttnBlock) void attend_kernel(
     int H_q, int H_kv, int max_pages, int k_list, int pgsz, int lg_sub,
     const QT* __restrict__ q, const KT* __restrict__ k_cache, const KT* __restrict__ v_cache,
     const int32_t* __restrict__ page_table, const int32_t* __restrict__ seq_lens,
     const int32_t* __restrict__ page_ids, int pages_per_split, int n_splits,
-    float* __restrict__ partial) {
-  __shared__ float sq[kMaxGroup][kDim];
-  __shared__ float sK[kPage][kDim + 1];
-  __shared__ float sV[kPage][kDim];
-  __shared__ float sP[kMaxGroup][kPage];
-  __shared__ float sO[kMaxGroup][kDim];
-  __shared__ float sM[kMaxGroup], sL[kMaxGroup], sScale[kMaxGroup];
+    float* __restrict__ partial, float* __restrict__ out, float* __restrict__ out_lse) {
+  __shared__ float sO[16][kDim + 4];
+  __shared__ float sM[16], sL[16];
 
-  const int split = blockIdx.x, h = blockIdx.y, s = blockIdx.z;
-  const int tid = threadIdx.x;
+  const int split = blockIdx.x % n_splits, g0 = blockIdx.x / n_splits * kHeads;
+  const int h = blockIdx.y, s = blockIdx.z;
+  const int tid = threadIdx.x, i = tid >> 4, seg = tid & 15;
   const int G = H_q / H_kv;
   const int L = seq_lens[s];
   const int n = (L + pgsz - 1) / pgsz;
   const float zscale = 1.0f / sqrtf((float)kDim);
-
-  for (int e = tid; e < G * kDim; e += kAttnBlock) {
-    sq[e / kDim][e % kDim] = ld(q, ((long)s * H_q + h * G) * kDim + e);
-    sO[e / kDim][e % kDim] = 0.0f;
-  }
-  for (int g = tid; g < G; g += kAttnBlock) { sM[g] = -INFINITY; sL[g] = 0.0f; }
-  __syncthreads();
+  const bool q_al = !(reinterpret_cast<uintptr_t>(q) & 15);
+  const bool kv_al = !((reinterpret_cast<uintptr_t>(k_cache) | reinterpret_cast<uintptr_t>(v_cache)) & 15);
 
   const int t0 = split * pages_per_split;
+  float qr[kHeads][8], o[kHeads][8], m[kHeads], l[kHeads];
+#pragma unroll
+  for (int g = 0; g < kHeads; ++g) {
+    load8(q + ((long)s * H_q + h * G + min(g0 + g, G - 1)) * kDim + 8 * seg, q_al, qr[g]);
+    m[g] = -INFINITY;
+    l[g] = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[g][e] = 0.0f;
+  }
   for (int t = t0; t < t0 + pages_per_split; ++t) {
     const int entry = t >> lg_sub, sub = t & ((1 << lg_sub) - 1);
     int id;
@@ -69,58 +112,65 @@ __global__ __launch_bounds__(kAttnBlock) void attend_kernel(
       id = entry;
     }
     if (id < 0 || id >= n) continue;  // uniform across the block
-    const int tok0 = id * pgsz + sub * kPage;
-    if (tok0 >= L) continue;
+    const int tok = id * pgsz + sub * kPage + i;
+    if (tok - i >= L) continue;
     const long blk = page_table[(long)s * max_pages + id];
-    const int valid = min(kPage, L - tok0);
-    const long base = ((blk * H_kv + h) * pgsz + sub * kPage) * kDim;
-    for (int e = tid; e < kPage * kDim; e += kAttnBlock) {
-      sK[e / kDim][e % kDim] = ld(k_cache, base + e);
-      sV[e / kDim][e % kDim] = ld(v_cache, base + e);
-    }
-    __syncthreads();
-    for (int e = tid; e < G * kPage; e += kAttnBlock) {
-      const int g = e / kPage, i = e % kPage;
-      float z = -INFINITY;
-      if (i < valid) {
-        float acc = 0.0f;
-        for (int c = 0; c < kDim; ++c) acc = fmaf(sq[g][c], sK[i][c], acc);
-        z = acc * zscale;
+    const long base = (((blk * H_kv + h) * pgsz + sub * kPage) + i) * kDim + 8 * seg;
+    float kr[8], vr[8];
+    load8(k_cache + base, kv_al, kr);
+    load8(v_cache + base, kv_al, vr);
+#pragma unroll
+    for (int g = 0; g < kHeads; ++g) {
+      float acc = 0.0f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc = fmaf(qr[g][e], kr[e], acc);
+      acc = row16_sum(acc);
+      if (tok < L) {  // uniform across the row
+        const float z = acc * zscale;
+        const float mx = fmaxf(m[g], z);
+        const float sc = (m[g] == -INFINITY) ? 0.0f : __expf(m[g] - mx);
+        const float w = (z == -INFINITY) ? 0.0f : __expf(z - mx);
+        l[g] = fmaf(l[g], sc, w);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[g][e] = fmaf(o[g][e], sc, w * vr[e]);
+        m[g] = mx;
       }
-      sP[g][i] = z;
     }
-    __syncthreads();
-    for (int g = tid; g < G; g += kAttnBlock) {
-      float mx = sM[g];
-      for (int i = 0; i < kPage; ++i) mx = fmaxf(mx, sP[g][i]);
-      const float sc = (sM[g] == -INFINITY) ? 0.0f : __expf(sM[g] - mx);
-      float l = sL[g] * sc;
-      for (int i = 0; i < kPage; ++i) {
-        const float w = (sP[g][i] == -INFINITY) ? 0.0f : __expf(sP[g][i] - mx);
-        sP[g][i] = w;
-        l += w;
-      }
-      sM[g] = mx;
-      sL[g] = l;
-      sScale[g] = sc;
-    }
-    __syncthreads();
-    for (int e = tid; e < G * kDim; e += kAttnBlock) {
-      const int g = e / kDim, c = e % kDim;
-      float acc = sO[g][c] * sScale[g];
-      for (int i = 0; i < kPage; ++i) acc = fmaf(sP[g][i], sV[i][c], acc);
-      sO[g][c] = acc;
-    }
-    __syncthreads();
   }
-  for (int e = tid; e < G * (kDim + 2); e += kAttnBlock) {
-    const int g = e / (kDim + 2), c = e % (kDim + 2);
-    const long row = (long)s * H_q + h * G + g;
-    float v = c < kDim ? sO[g][c] : (c == kDim ? sM[g] : sL[g]);
-    partial[(row * n_splits + split) * (kDim + 2) + c] = v;
+  // ---- the 16 rows of each head combined
+#pragma unroll
+  for (int g = 0; g < kHeads; ++g) {
+    if (g0 + g >= G) break;
+    if (g) __syncthreads();
+    *reinterpret_cast<float4*>(&sO[i][8 * seg]) = make_float4(o[g][0], o[g][1], o[g][2], o[g][3]);
+    *reinterpret_cast<float4*>(&sO[i][8 * seg + 4]) = make_float4(o[g][4], o[g][5], o[g][6], o[g][7]);
+    if (seg == 0) { sM[i] = m[g]; sL[i] = l[g]; }
+    __syncthreads();
+    if (tid < kDim) {
+      float mx = -INFINITY;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sM[r]);
+      float acc = 0.0f, ls = 0.0f;
+      if (mx > -INFINITY) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float wt = sM[r] == -INFINITY ? 0.0f : __expf(sM[r] - mx);
+          ls = fmaf(sL[r], wt, ls);
+          acc = fmaf(sO[r][tid], wt, acc);
+        }
+      }
+      const long row = (long)s * H_q + h * G + g0 + g;
+      if (n_splits == 1) {
+        out[row * kDim + tid] = ls > 0.0f ? acc / ls : 0.0f;
+        if (tid == 0 && out_lse) out_lse[row] = ls > 0.0f ? mx + logf(ls) : -INFINITY;
+      } else {
+        float* pr = partial + (row * n_splits + split) * (kDim + 2);
+        pr[tid] = acc;
+        if (tid < 2) pr[kDim + tid] = tid ? ls : mx;
+      }
+    }
   }
 }
-
 
 // ---------------------------------------------------------------- MFMA path
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
@@ -198,14 +248,17 @@ struct SelTable {
 // unit and 64 stand-in loads in every block past its sequence's end, 214 us now, 5.2
 // TB/s, the rate of a plain copy).
 // kNK: survivors per lane of the selection merge (64 kNK per wave).
-template <bool kSelect, int kPPW, int kNK>
+// kOne: the list is one block's, which writes the output itself (the step of 64 sequences
+// x 8 KV heads, 16 entries each: 167.5 -> 161.5 us without the merge launch).  An instance
+// of its own: the same branch taken at run time cost 0.8 us of 130.6 where the list is split.
+template <bool kSelect, int kPPW, int kNK, bool kOne>
 __global__ __launch_bounds__(256) void attend_mfma_kernel(
     int H_q, int H_kv, int max_pages, int k_list, int pgsz, int lg_sub,
     const uint16_t* __restrict__ q,
     const uint16_t* __restrict__ k_cache, const uint16_t* __restrict__ v_cache,
     const int32_t* __restrict__ page_table, const int32_t* __restrict__ seq_lens,
     const int32_t* __restrict__ page_ids, int pages_per_split, int n_splits,
-    float* __restrict__ partial, SelTable tb) {
+    float* __restrict__ partial, float* __restrict__ out, float* __restrict__ out_lse, SelTable tb) {
   __shared__ float sO[4][kDim][kMaxGroup + 1];
   __shared__ float sM[4][kMaxGroup], sL[4][kMaxGroup];
   __shared__ int32_t s_tab[kSelect ? kFastK + 2 : 1], s_blk[kSelect ? kFastK + 2 : 1];
@@ -230,8 +283,11 @@ __global__ __launch_bounds__(256) void attend_mfma_kernel(
     // no list and past the sequence's end: an empty partial
     for (int e = tid; e < G * (kDim + 2); e += 256) {
       const int g = e / (kDim + 2), c = e % (kDim + 2);
-      partial[(((long)s * H_q + h * G + g) * n_splits + split) * (kDim + 2) + c] =
-          c == kDim ? -INFINITY : 0.0f;
+      const long row = (long)s * H_q + h * G + g;
+      const float v = c == kDim ? -INFINITY : 0.0f;
+      if constexpr (!kOne) partial[(row * n_splits + split) * (kDim + 2) + c] = v;
+      else if (c < kDim) out[row * kDim + c] = v;
+      else if (c == kDim && out_lse) out_lse[row] = v;
     }
     return;
   }
@@ -432,9 +488,14 @@ __global__ __launch_bounds__(256) void attend_mfma_kernel(
         if (c < kDim) acc += sO[w][c][g] * wt;
       }
     }
-    const float v = c < kDim ? acc : (c == kDim ? (mx == -INFINITY ? mx : mx * kLn2) : ls);
+    const float mn = mx == -INFINITY ? mx : mx * kLn2;
     const long row = (long)s * H_q + h * G + g;
-    partial[(row * n_splits + split) * (kDim + 2) + c] = v;
+    if constexpr (kOne) {  // as merge_kernel forms it
+      if (c < kDim) out[row * kDim + c] = ls > 0.0f ? acc / ls : 0.0f;
+      else if (c == kDim && out_lse) out_lse[row] = ls > 0.0f ? mn + logf(ls) : -INFINITY;
+    } else {
+      partial[(row * n_splits + split) * (kDim + 2) + c] = c < kDim ? acc : (c == kDim ? mn : ls);
+    }
   }
 }
 
@@ -482,13 +543,20 @@ __global__ __launch_bounds__(kDim) void merge_kernel(int H_q, int n_splits,
 template <typename QT, typename KT>
 void launch_typed(const locks_cfg_t& c, const void* q, const void* k_cache, const void* v_cache,
                   const int32_t* page_table, const int32_t* seq_lens, const int32_t* page_ids,
-                  int pages_per_split, int n_splits, float* partial, hipStream_t st) {
-  hipLaunchKernelGGL((attend_kernel<QT, KT>), dim3(n_splits, c.num_kv_heads, c.num_seqs),
-                     dim3(kAttnBlock), 0, st, c.num_q_heads, c.num_kv_heads, c.max_pages_per_seq,
-                     page_budget(c), c.page_size, sub_page_log2(c), static_cast<const QT*>(q),
-                     static_cast<const KT*>(k_cache),
-                     static_cast<const KT*>(v_cache), page_table, seq_lens, page_ids,
-                     pages_per_split, n_splits, partial);
+                  int pages_per_split, int n_splits, float* partial, float* out, float* out_lse,
+                  hipStream_t st) {
+  const int G = c.num_q_heads / c.num_kv_heads;
+#define LOCKS_ATTEND(HH)                                                                       \
+  hipLaunchKernelGGL((attend_kernel<QT, KT, HH>),                                              \
+                     dim3(n_splits * ((G + HH - 1) / HH), c.num_kv_heads, c.num_seqs),         \
+                     dim3(kAttnBlock), 0, st, c.num_q_heads, c.num_kv_heads,                   \
+                     c.max_pages_per_seq, page_budget(c), c.page_size, sub_page_log2(c),       \
+                     static_cast<const QT*>(q), static_cast<const KT*>(k_cache),               \
+                     static_cast<const KT*>(v_cache), page_table, seq_lens, page_ids,          \
+                     pages_per_split, n_splits, partial, out, out_lse)
+  if (G == 1) LOCKS_ATTEND(1);
+  else LOCKS_ATTEND(4);
+#undef LOCKS_ATTEND
 }
 
 // bf16 MFMA kernel with the page count per wave fixed at compile time where the
@@ -497,19 +565,21 @@ template <bool kSelect>
 void launch_mfma(const locks_cfg_t& c, dim3 grid, hipStream_t st, const uint16_t* q,
                  const uint16_t* k_cache, const uint16_t* v_cache, const int32_t* page_table,
                  const int32_t* seq_lens, const int32_t* page_ids, int pages_per_split,
-                 int n_splits, float* partial, SelTable tb) {
+                 int n_splits, float* partial, float* out, float* out_lse, SelTable tb) {
   const int ppw = pages_per_split % 4 == 0 ? pages_per_split / 4 : 0;
-  // survivors held per lane: 2, 4 or the cap's 8
+  // survivors held per lane: 2, 4 or the cap's 8 (without a selection none)
   const int held = kSelect ? tb.n_rows * tb.width : 0;
-#define LOCKS_ATTEND_MFMA(P)                              \
-  if (held <= 2 * 256) LOCKS_ATTEND_MFMA_N(P, 2);        \
-  else if (held <= 4 * 256) LOCKS_ATTEND_MFMA_N(P, 4);   \
-  else LOCKS_ATTEND_MFMA_N(P, kUnionNK)
+#define LOCKS_ATTEND_MFMA(P)                                               \
+  if (held <= 2 * 256) LOCKS_ATTEND_MFMA_N(P, 2);                          \
+  else if (held <= 4 * 256) LOCKS_ATTEND_MFMA_N(P, (kSelect ? 4 : 2));     \
+  else LOCKS_ATTEND_MFMA_N(P, (kSelect ? kUnionNK : 2))
 #define LOCKS_ATTEND_MFMA_N(P, NK)                                                             \
-  hipLaunchKernelGGL((attend_mfma_kernel<kSelect, P, NK>), grid, dim3(256), 0, st, c.num_q_heads, \
+  hipLaunchKernelGGL((n_splits == 1 ? attend_mfma_kernel<kSelect, P, NK, true>                  \
+                                    : attend_mfma_kernel<kSelect, P, NK, false>),               \
+                     grid, dim3(256), 0, st, c.num_q_heads,                                     \
                      c.num_kv_heads, c.max_pages_per_seq, page_budget(c), c.page_size,          \
                      sub_page_log2(c), q, k_cache, v_cache, page_table, seq_lens, page_ids,     \
-                     pages_per_split, n_splits, partial, tb)
+                     pages_per_split, n_splits, partial, out, out_lse, tb)
   switch (ppw) {
     case 1: LOCKS_ATTEND_MFMA(1); break;
     case 2: LOCKS_ATTEND_MFMA(2); break;
@@ -532,18 +602,19 @@ hipError_t launch_attend(const locks_cfg_t& c, const void* q, const void* k_cach
     launch_mfma<false>(c, dim3(n_splits, c.num_kv_heads, c.num_seqs), st,
                        static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k_cache),
                        static_cast<const uint16_t*>(v_cache), page_table, seq_lens, page_ids,
-                       pages_per_split, n_splits, partial, SelTable{});
+                       pages_per_split, n_splits, partial, out, out_lse, SelTable{});
   else if (qb)
     launch_typed<uint16_t, float>(c, q, k_cache, v_cache, page_table, seq_lens, page_ids,
-                                  pages_per_split, n_splits, partial, st);
+                                  pages_per_split, n_splits, partial, out, out_lse, st);
   else if (kb)
     launch_typed<float, uint16_t>(c, q, k_cache, v_cache, page_table, seq_lens, page_ids,
-                                  pages_per_split, n_splits, partial, st);
+                                  pages_per_split, n_splits, partial, out, out_lse, st);
   else
     launch_typed<float, float>(c, q, k_cache, v_cache, page_table, seq_lens, page_ids,
-                               pages_per_split, n_splits, partial, st);
-  hipLaunchKernelGGL(merge_kernel, dim3(c.num_q_heads, c.num_seqs), dim3(kDim), 0, st,
-                     c.num_q_heads, n_splits, partial, out, out_lse);
+                               pages_per_split, n_splits, partial, out, out_lse, st);
+  if (n_splits > 1)
+    hipLaunchKernelGGL(merge_kernel, dim3(c.num_q_heads, c.num_seqs), dim3(kDim), 0, st,
+                       c.num_q_heads, n_splits, partial, out, out_lse);
   return hipGetLastError();
 }
 
@@ -562,9 +633,10 @@ hipError_t launch_attend_select(const locks_cfg_t& c, const void* q, const void*
   launch_mfma<true>(c, dim3(n_splits, c.num_kv_heads, c.num_seqs), st,
                     static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k_cache),
                     static_cast<const uint16_t*>(v_cache), page_table, seq_lens, nullptr,
-                    pages_per_split, n_splits, partial, tb);
-  hipLaunchKernelGGL(merge_kernel, dim3(c.num_q_heads, c.num_seqs), dim3(kDim), 0, st,
-                     c.num_q_heads, n_splits, partial, out, out_lse);
+                    pages_per_split, n_splits, partial, out, out_lse, tb);
+  if (n_splits > 1)
+    hipLaunchKernelGGL(merge_kernel, dim3(c.num_q_heads, c.num_seqs), dim3(kDim), 0, st,
+                       c.num_q_heads, n_splits, partial, out, out_lse);
   return hipGetLastError();
 }
 

@@ -396,3 +396,50 @@ def test_selection_chunk_sizes(G, copies):
         c = t.view(torch.int32).view(copies, 3, *t.shape[1:])  # bits: open pages' scores are NaN
         assert torch.equal(c, c[:1].expand_as(c))
     _step_against_oracle(d, refs, ids, sel, out, lse)
+
+
+@pytest.mark.parametrize("G,page,q,kv,copies", [
+    (1, 16, "fp32", "fp32", 1), (3, 32, "bf16", "fp32", 1), (5, 16, "fp32", "bf16", 1),
+    (16, 64, "fp32", "fp32", 1), (5, 16, "fp32", "fp32", 172), (1, 16, "bf16", "fp32", 172),
+    (4, 16, "bf16", "bf16", 172), (16, 32, "bf16", "bf16", 172)])
+def test_attention_head_groups_and_whole_lists(G, page, q, kv, copies):
+    """Attention of fp32 tensors at every count of heads a block can hold, and lists that
+    one block takes whole (many sequences): lengths around a page, a single token, an empty
+    sequence, list entries left open; K and V 4 or 2 bytes off a 16-byte boundary where the
+    vector-ALU kernel reads them."""
+    lens = [page * 9 + 3, 1, 0, page * 8]
+    spec = WorkloadSpec("groups", len(lens), 2 * G, 2, lens, 8, 12 * page, kv, q, page_size=page)
+    d = Dev(build_workload(spec, 29))
+    c = d.cfg
+    ids = torch.full((len(lens), 2, c.k), -1, dtype=torch.int32, device=d.device)
+    for s, L in enumerate(lens):
+        n = -(-L // page)
+        ids[s, :, :n] = torch.arange(n, device=d.device)
+    want = [[O.dense_step(*(d.unit(s, h)[i] for i in (2, 0, 1))) if lens[s] else None
+             for h in range(2)] for s in range(len(lens))]
+    if kv == "fp32" or q == "fp32":
+        def off(t):
+            buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+            buf[1:] = t.flatten()
+            return buf[1:].view(t.shape)
+        d.k, d.v, d.q = off(d.k), off(d.v), off(d.q)
+    c.num_seqs = len(lens) * copies
+    d.q, d.pt, d.sl = d.q.repeat(copies, 1, 1) if copies > 1 else d.q, \
+        d.pt.repeat(copies, 1), d.sl.repeat(copies)
+    d.ws = B.alloc_workspace(c, d.device)
+    for out, lse in (B.sparse_attend(c, d.q, d.k, d.v, d.pt, d.sl, ids.repeat(copies, 1, 1), d.ws),
+                     B.dense_attend(c, d.q, d.k, d.v, d.pt, d.sl, d.ws)):
+        torch.cuda.synchronize()
+        for t in (out, lse):
+            x = t.view(copies, len(lens), *t.shape[1:])
+            assert torch.equal(x, x[:1].expand_as(x))
+        for s in range(len(lens)):
+            for h in range(2):
+                hs = slice(h * G, (h + 1) * G)
+                got = out[s, hs].double().cpu().numpy()
+                if not lens[s]:
+                    assert not got.any() and torch.isneginf(lse[s, hs]).all()
+                    continue
+                o, l = want[s][h]
+                assert max(rel_l2(got[g], o[g]) for g in range(G)) <= OUT_TOL
+                np.testing.assert_allclose(lse[s, hs].double().cpu().numpy(), l, atol=LSE_TOL)
