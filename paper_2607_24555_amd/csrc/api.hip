@@ -189,10 +189,13 @@ int dense_splits(const locks_cfg_t& c, int pps) {
 }
 
 // Blocks the workspace plan holds dense partials for, two per compute unit, and blocks
-// the launch asks for: with ragged lengths about half of the grid is past its sequence's
-// end, and four per compute unit balance the rest (8 sequences of 3K to 65K tokens, 8 KV
-// heads: 237 us at 512 blocks, 214 at 1,024, 216 at 2,048, 241 at 4,096, where the
-// per-block latency shows).
+// below which the launch of a batch halves the whole 256: with ragged lengths about half of
+// the grid is past its sequence's end, and four per compute unit balance the rest (8
+// sequences of 3K to 65K tokens, 8 KV heads: 237 us at 512 blocks, 214 at 1,024, 216 at
+// 2,048, 241 at 4,096, where the per-block latency shows).  One sequence is not ragged and
+// pays for the partials (1M, 2 KV heads: 61.4 us at the plan's split, 70.0 at half of it,
+// pages in the last-level cache), and smaller splits are as many blocks as they need (4 x
+// 16K, 8 KV heads: 13.6 us at 64 units a block, 14.6 at 32).
 constexpr long kDensePlanBlocks = 512, kDenseBlocks = 1024;
 
 // The build for the configuration's page size: the register-resident kernel of
@@ -393,7 +396,10 @@ int locks_dense_attend(const locks_cfg_t* cfg, const void* q, const void* k_cach
   // split always fits
   const WsPlan p = plan_workspace(*cfg);
   const size_t row = (size_t)cfg->num_seqs * cfg->num_q_heads * (kDim + 2) * sizeof(float);
-  int pps = dense_pages_per_split(*cfg, kDenseBlocks);
+  int pps = dense_pages_per_split(*cfg, kDensePlanBlocks);
+  if (cfg->num_seqs > 1 && pps == kDensePagesPerSplit &&
+      (long)cfg->num_seqs * cfg->num_kv_heads * dense_splits(*cfg, pps) < kDenseBlocks)
+    pps /= 2;
   while (pps < kDensePagesPerSplit && row * (size_t)dense_splits(*cfg, pps) > p.chk_pt_off) pps *= 2;
   return hip_status(launch_attend(*cfg, q, k_cache, v_cache, page_table, seq_lens, nullptr, pps,
                                   dense_splits(*cfg, pps), static_cast<float*>(ws), out, out_lse,
