@@ -64,20 +64,32 @@ __device__ __forceinline__ float lds_f16(const uint8_t* p) {
   return (float)*reinterpret_cast<const _Float16*>(p);
 }
 
+// log2(2^a + 2^b)
+__device__ __forceinline__ float lse2_log2(float a, float b) {
+  const float mx = fmaxf(a, b);
+  return mx + __builtin_amdgcn_logf(__builtin_amdgcn_exp2f(a - mx) + __builtin_amdgcn_exp2f(b - mx));
+}
+
+// Sum over lanes l, l ^ 32 and over lanes l, l ^ 16.
+__device__ __forceinline__ float swap32_sum(float v) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+__device__ __forceinline__ float swap16_sum(float v) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+
 // Log-sum-exp, log2 domain, over lanes {l, l ^ 16} (V = 2) or {l, l ^ 16, l ^ 32,
 // l ^ 48} (V = 4); each of those lanes gets the same bits.
 template <int V>
 __device__ __forceinline__ float merge_sub_lse(float v) {
-  auto lse2 = [](float a, float b) {
-    const float mx = fmaxf(a, b);
-    return mx + __builtin_amdgcn_logf(__builtin_amdgcn_exp2f(a - mx) + __builtin_amdgcn_exp2f(b - mx));
-  };
   if (V == 4) {
     auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = lse2(__uint_as_float(p[0]), __uint_as_float(p[1]));
+    v = lse2_log2(__uint_as_float(p[0]), __uint_as_float(p[1]));
   }
   auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return lse2(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  return lse2_log2(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
 // Reduction over the four lanes {l, l^16, l^32, l^48} with two VALU lane swaps.
@@ -125,6 +137,22 @@ __device__ __forceinline__ void merge_lanes_mod(float& m, float& l) {
             : 0.0f;
     m = mm;
   }
+}
+
+// Sums of 2^z over a page's tokens are taken without their max: z are the logits minus the
+// centroid logit, which sum to about 0 over the page.  Outside this range (a token 83 nats
+// above that mean; every token 70 below it, where a record's coefficients are not centred)
+// a sum loses bits to the ends of float32 and is taken again with a shift: the fixed
+// kHighShift, for which sums of 2^116 to 2^336 are in the range, or the max.
+constexpr float kSumMin = 0x1p-100f, kSumMax = 0x1p120f, kLog2SumMin = -100.0f, kHighShift = 216.0f;
+
+// Log-sum-exp, log2 domain, of the 4 x 4 values that lanes l, l ^ 16, l ^ 32, l ^ 48 hold;
+// each of those lanes gets it.
+__device__ __forceinline__ float max_shifted_lse(const float (&z)[4]) {
+  const float shift = red4_max(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])));
+  const float sm = (__builtin_amdgcn_exp2f(z[0] - shift) + __builtin_amdgcn_exp2f(z[1] - shift)) +
+                   (__builtin_amdgcn_exp2f(z[2] - shift) + __builtin_amdgcn_exp2f(z[3] - shift));
+  return shift + __builtin_amdgcn_logf(red4_sum(sm));
 }
 
 typedef int i4v __attribute__((ext_vector_type(4)));

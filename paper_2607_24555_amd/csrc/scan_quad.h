@@ -29,14 +29,15 @@
 // Stage 1 then runs once per four pages: at V = 4 a quad is one page, lane (grp, col)
 // gets p(page grp of the step, l, head g), and three row swaps (16 and 32 lanes)
 // broadcast page u's rows for quad u; at V = 2 a pass covers two quads, its rows
-// ordered so that one 16-lane swap yields both quads' layouts.  The sub-page LSEs of a
-// page are merged over their lanes before the page's score is stored.
+// ordered so that one 16-lane swap yields both quads' layouts.  The sums of a page's
+// sub-pages are added over their lanes before the logarithm.
 //
 // Bound: at 16-token pages the scattered record gather (8 x 128K, four-head groups: 94 us,
 // 4.6 TB/s, where the gather alone runs at 5.2 to 5.7); at 32 and 64 tokens the vector
-// ALU's work per sub-page, so those instances are held to 168 registers (three waves per
-// SIMD) and the per-step tail above is shared by the quads: 8 x 128K in 64-token pages
-// 60 -> 44 us.
+// ALU's work per sub-page, so the per-step tail above is shared by the quads and the
+// instances of four columns are held to 168 registers (three waves per SIMD; at two, 32-token
+// pages take 52 us for 46): 8 x 128K in 64-token pages 38.5 us.  Those of eight columns take
+// 197 to 229 registers, two waves.
 #pragma once
 
 #include "locks_internal.h"
@@ -46,11 +47,6 @@
 
 namespace locks {
 namespace {
-
-__device__ __forceinline__ float lse2_log2(float a, float b) {
-  const float mx = fmaxf(a, b);
-  return mx + __builtin_amdgcn_logf(__builtin_amdgcn_exp2f(a - mx) + __builtin_amdgcn_exp2f(b - mx));
-}
 
 // the value of lane l ^ X within a 16-lane row, X = 4 or 8
 template <int X>
@@ -66,7 +62,7 @@ __device__ __forceinline__ float row_xor(float v) {
 }
 
 template <typename QT, int HG, int kSteps, int V>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void scan_quad_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 4 && V > 1 ? 3 : 2))) void scan_quad_kernel(
     int H_q, int H_kv, int G, int max_pages, const QT* __restrict__ q,
     const uint8_t* __restrict__ summ, uint32_t summ_bytes, const int32_t* __restrict__ page_table,
     const int32_t* __restrict__ seq_lens, float* __restrict__ s_hat, SHatLayout lay,
@@ -182,18 +178,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
       for (int u = 0; u < kNP; ++u) ld_ms(o0, u);
     };
 
+    bool low = false;    // a page's sum was too small
+    uint64_t force = 0;  // ~0: every sum is taken with its max shifted out
     // kN consecutive 16-page steps from page `start` whose first step's
     // registers are loaded (blk_next: blocks of the second step's pages), fully
     // unrolled so that every wait for a prefetched register counts exactly the
     // loads issued after it.
-    // The sums of 2^z are taken without a max: z are the logits minus the centroid
-    // logit and sum to ~0 over a page's tokens, so only a spread of more than ~88 nats
-    // overflows; a page score that is not finite sets `bad`, and the wave's pages are
-    // then scanned again with every sum shifted by its max (kSafe).
-    bool bad = false;
-    auto run = [&](int start, auto n_tag, auto safe_tag, int blk_next) {
+    auto run = [&](int start, auto n_tag, int blk_next) {
       constexpr int kN = decltype(n_tag)::value;
-      constexpr bool kSafe = decltype(safe_tag)::value != 0;
 #pragma unroll
       for (int t_step = 0; t_step < kN; ++t_step) {
         const bool pf = t_step + 1 < kN;
@@ -245,8 +237,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
         }
 
         float bq[kShare][8];  // shared stage 1: the values of the step's quads
-        // sum of 2^z over the lane's four tokens (kSafe: the pass's LSE, in every row)
-        float ps[4][kNP];
+        float ps[4][kNP];     // sum of 2^z over the lane's four tokens
+        float wide[kNP];      // LSE, max shifted out, of the lane's own pages (-inf: not needed)
+        bool any_wide = false;
+#pragma unroll
+        for (int u = 0; u < kNP; ++u) wide[u] = -INFINITY;
         auto keep = [&](int u, float s2) {  // store and count the page score
           const int page = page0 + own(u);
           const bool live = page < n_c && own(u) % V == 0;
@@ -326,6 +321,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
             bl[e] = lo[0];
             bl[e + 1] = lo[1];
           }
+          float z[kNP][4];
+          uint64_t far = force;  // lanes whose sum is too large
           static_for_int<kNP>([&](auto t_tag) __attribute__((always_inline)) {
             constexpr int t = decltype(t_tag)::value;
             uint4 At = A;
@@ -336,58 +333,60 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
             f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
             acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, At), bh, acc, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, At), bl, acc, 0, 0, 0);
-            float z[4];
             const h2 c01 = as_h2(cs[Q][t].x), c23 = as_h2(cs[Q][t].y);
-            z[0] = (float)c01.x * acc[0];
-            z[1] = (float)c01.y * acc[1];
-            z[2] = (float)c23.x * acc[2];
-            z[3] = (float)c23.y * acc[3];
+            z[t][0] = (float)c01.x * acc[0];
+            z[t][1] = (float)c01.y * acc[1];
+            z[t][2] = (float)c23.x * acc[2];
+            z[t][3] = (float)c23.y * acc[3];
             if (pf) ld_cs(on, Q, t);
-            if constexpr (kSafe) {
-              const float shift = red4_max(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])));
-              const float sm = __builtin_amdgcn_exp2f(z[0] - shift) + __builtin_amdgcn_exp2f(z[1] - shift) +
-                               __builtin_amdgcn_exp2f(z[2] - shift) + __builtin_amdgcn_exp2f(z[3] - shift);
-              ps[Q][t] = shift + __builtin_amdgcn_logf(red4_sum(sm));
-            } else {
-              ps[Q][t] = __builtin_amdgcn_exp2f(z[0]) + __builtin_amdgcn_exp2f(z[1]) +
-                         __builtin_amdgcn_exp2f(z[2]) + __builtin_amdgcn_exp2f(z[3]);
-            }
+            ps[Q][t] = __builtin_amdgcn_exp2f(z[t][0]) + __builtin_amdgcn_exp2f(z[t][1]) +
+                       __builtin_amdgcn_exp2f(z[t][2]) + __builtin_amdgcn_exp2f(z[t][3]);
+            far |= __ballot(!(ps[Q][t] <= kSumMax));
           });
+          // tokens spread too widely: taken again while the quad's logits are in registers
+          // (8 x 128K, four-head groups, every page so: 97 us, and 150 where the wave's
+          // pages were scanned a second time; pages of ordinary spread 94)
+          if (__builtin_expect(far != 0, 0)) {
+            any_wide = true;
+#pragma unroll
+            for (int t = 0; t < kNP; ++t) {
+              const float l2 = max_shifted_lse(z[t]);
+              wide[t] = grp == Q ? l2 : wide[t];
+            }
+          }
         });
         __builtin_amdgcn_sched_barrier(0);
-        // ---- the LSEs of the lane's own pages: totals, four passes at a time
-        float s2[kNP];
+        // ---- the LSEs of the lane's own pages: totals, four passes at a time; the sums of
+        // a page's sub-pages added (every lane of the page gets the total)
+        float l2[kNP];
 #pragma unroll
-        for (int u = 0; u < kNP; ++u) {
-          float l2;
-          if constexpr (kSafe)
-            l2 = grp == 0 ? ps[0][u] : (grp == 1 ? ps[1][u] : (grp == 2 ? ps[2][u] : ps[3][u]));
-          else
-            l2 = __builtin_amdgcn_logf(reduce4(ps[0][u], ps[1][u], ps[2][u], ps[3][u]));
-          s2[u] = am[u] * ((float)as_h2(msw[u]).x * QD.inv_scale) + l2;
-          if (pf) ld_ms(on, u);
-          bad |= !(fabsf(s2[u]) < INFINITY);
-        }
-        // sub-pages of a page: their LSEs merged (every lane of the page gets it)
-        if constexpr (V > 1) {
+        for (int u = 0; u < kNP; ++u) l2[u] = reduce4(ps[0][u], ps[1][u], ps[2][u], ps[3][u]);
+        if (__builtin_expect(!any_wide, 1)) {
 #pragma unroll
           for (int u = 0; u < kNP; ++u) {
-            s2[u] = lse2_log2(s2[u], row_xor<HG>(s2[u]));
-            if (HG == 4 && V == 4) s2[u] = lse2_log2(s2[u], row_xor<8>(s2[u]));
+            if (V > 1) l2[u] += row_xor<HG>(l2[u]);
+            if (V == 4 && HG == 4) l2[u] += row_xor<8>(l2[u]);
           }
-          if constexpr (HG == 8 && V == 4) s2[0] = lse2_log2(s2[0], s2[1]);
+          if constexpr (V == 4 && HG == 8) l2[0] += l2[1];
+#pragma unroll
+          for (int u = 0; u < kNP; ++u) l2[u] = __builtin_amdgcn_logf(l2[u]);
+        } else {
+#pragma unroll
+          for (int u = 0; u < kNP; ++u) {
+            l2[u] = wide[u] != -INFINITY ? wide[u] : __builtin_amdgcn_logf(l2[u]);
+            if (V > 1) l2[u] = lse2_log2(l2[u], row_xor<HG>(l2[u]));
+            if (V == 4 && HG == 4) l2[u] = lse2_log2(l2[u], row_xor<8>(l2[u]));
+          }
+          if constexpr (V == 4 && HG == 8) l2[0] = lse2_log2(l2[0], l2[1]);
         }
 #pragma unroll
-        for (int u = 0; u < kNP; ++u)
-          if (!(HG == 8 && V == 4 && u == 1)) keep(u, s2[u]);
+        for (int u = 0; u < kNP; ++u) {
+          low |= l2[u] < kLog2SumMin;
+          const float s2 = am[u] * ((float)as_h2(msw[u]).x * QD.inv_scale) + l2[u];
+          if (pf) ld_ms(on, u);
+          if (!(HG == 8 && V == 4 && u == 1)) keep(u, s2);
+        }
         blk_next = blk_after;
-      }
-    };
-    auto run_each = [&](auto safe_tag) {
-#pragma unroll 1
-      for (int t = 0; t < n_steps; ++t) {
-        load_step(lane_block_clamped<V>(pt_row, first + 16 * t, n_c, lane));
-        run(first + 16 * t, IntTag<1>{}, safe_tag, 0);
       }
     };
     // with several steps a wave, the first step's records are on their way while the
@@ -406,14 +405,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
     inv_m = mine ? QD.inv_scale : 0.0f;
     if (n_steps == kSteps) {
       if (kSteps == 1) load_step(blk0);
-      run(first, IntTag<kSteps>{}, IntTag<0>{}, blk1);
-    } else {
-      run_each(IntTag<0>{});
+      run(first, IntTag<kSteps>{}, blk1);
     }
-    if (__any(bad)) {
+    for (bool again = n_steps != kSteps;; again = true) {
+      if (again)
+#pragma unroll 1
+        for (int t = 0; t < n_steps; ++t) {
+          load_step(lane_block_clamped<V>(pt_row, first + 16 * t, n_c, lane));
+          run(first + 16 * t, IntTag<1>{}, 0);
+        }
+      if (force || !__any(low)) break;
+      force = ~0ull;
       run_m = -INFINITY;
       run_s = 0.0f;
-      run_each(IntTag<1>{});
     }
   }
   // ---- block partial (max, sum exp) per head over its pages, log2 domain: lane

@@ -138,14 +138,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
     // kN consecutive 16-page steps from page `start` whose first step's registers are
     // loaded (blk_next: blocks of the second step's pages), fully unrolled so that
     // every wait for a prefetched register counts exactly the loads issued after it.
-    // The sums of 2^z are taken without a max: z are the logits minus the centroid
-    // logit and sum to ~0 over a page's tokens, so only a spread of more than ~88 nats
-    // overflows; a page score that is not finite sets `bad`, and the wave's pages are
-    // then scanned again with every sum shifted by its max (kSafe).
-    bool bad = false;
-    auto run = [&](int start, auto n_tag, auto safe_tag, int blk_next) {
+    auto run = [&](int start, auto n_tag, int blk_next) {
       constexpr int kN = decltype(n_tag)::value;
-      constexpr bool kSafe = decltype(safe_tag)::value != 0;
 #pragma unroll
       for (int t_step = 0; t_step < kN; ++t_step) {
         const bool pf = t_step + 1 < kN;
@@ -193,17 +187,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
           ld_ms(on);
         }
 
-        // total, page LSE, store and running normaliser of (sub-)pages 4 u .. 4 u + 3
-        // (kSafe: ps[t] is already the LSE of (sub-)page 4 u + t, in every row)
-        auto finish = [&](auto u_tag, const float (&ps)[4]) {
+        // page LSE, store and running normaliser of (sub-)pages 4 u .. 4 u + 3 (l2: log2 of
+        // the sum of (sub-)page 4 u + grp)
+        auto finish = [&](auto u_tag, float l2) {
           constexpr int u = decltype(u_tag)::value;
           const int own = 4 * u + grp;
-          float l2;
-          if constexpr (kSafe) l2 = grp == 0 ? ps[0] : (grp == 1 ? ps[1] : (grp == 2 ? ps[2] : ps[3]));
-          else l2 = __builtin_amdgcn_logf(reduce4(ps[0], ps[1], ps[2], ps[3]));
           float s2 = am[u] * (row_bcast<u>(msf) * QD.inv_scale) + l2;
-          bad |= !(fabsf(s2) < INFINITY);
-          if constexpr (V > 1) s2 = merge_sub_lse<V>(s2);
           const int page = page0 + own;
           const bool live = page < n_c && own % V == 0;
           if (live && col < G) shat_lane[(long)(page / V) * lay.page] = s2 * 0.69314718055994531f;
@@ -252,7 +241,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
           // V quads of (sub-)pages: quad Qv covers sub-pages 4 Qv .. of the pair
           static_for_int<V>([&](auto v_tag) __attribute__((always_inline)) {
             constexpr int Qv = decltype(v_tag)::value, u = V * m + Qv;
-            float ps[4];
+            float ps[4], z[4][4];
             static_for_int<4>([&](auto t_tag) __attribute__((always_inline)) {
               constexpr int t = decltype(t_tag)::value, sp = 4 * u + t;
               const uint32_t w = cf[sp];
@@ -263,30 +252,41 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
               const h4 A{a01.x, a01.y, a23.x, a23.y};
               f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
               acc = __builtin_amdgcn_mfma_f32_16x16x16f16(A, bp[(4 * Qv + t) / V], acc, 0, 0, 0);
-              float z[4];
 #pragma unroll
-              for (int j = 0; j < 4; ++j) z[j] = row_bcast<sp>(csf[j]) * acc[j];
-              if constexpr (kSafe) {
-                const float shift = red4_max(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])));
-                const float sm = (__builtin_amdgcn_exp2f(z[0] - shift) + __builtin_amdgcn_exp2f(z[1] - shift)) +
-                                 (__builtin_amdgcn_exp2f(z[2] - shift) + __builtin_amdgcn_exp2f(z[3] - shift));
-                ps[t] = shift + __builtin_amdgcn_logf(red4_sum(sm));
-              } else {
-                ps[t] = (__builtin_amdgcn_exp2f(z[0]) + __builtin_amdgcn_exp2f(z[1])) +
-                        (__builtin_amdgcn_exp2f(z[2]) + __builtin_amdgcn_exp2f(z[3]));
-              }
+              for (int j = 0; j < 4; ++j) z[t][j] = row_bcast<sp>(csf[j]) * acc[j];
+              ps[t] = (__builtin_amdgcn_exp2f(z[t][0]) + __builtin_amdgcn_exp2f(z[t][1])) +
+                      (__builtin_amdgcn_exp2f(z[t][2]) + __builtin_amdgcn_exp2f(z[t][3]));
             });
-            finish(IntTag<u>{}, ps);
+            const float sm = reduce4(ps[0], ps[1], ps[2], ps[3]);
+            float tot = sm;  // of the page: the sums of its sub-pages added
+            if constexpr (V == 4) tot = swap32_sum(tot);
+            if constexpr (V > 1) tot = swap16_sum(tot);
+            float l2 = __builtin_amdgcn_logf(tot);
+            // tokens spread too widely: taken again from the logits in registers (1M, two KV
+            // heads, every page so: 29 us, and 54 where the wave's pages were scanned a second
+            // time; pages of ordinary spread 25.5)
+            if (__builtin_expect(__any(!(sm >= kSumMin && sm <= kSumMax)), 0)) {
+              float ph[4];
+#pragma unroll
+              for (int t = 0; t < 4; ++t)
+                ph[t] = (__builtin_amdgcn_exp2f(z[t][0] - kHighShift) + __builtin_amdgcn_exp2f(z[t][1] - kHighShift)) +
+                        (__builtin_amdgcn_exp2f(z[t][2] - kHighShift) + __builtin_amdgcn_exp2f(z[t][3] - kHighShift));
+              const float sh = reduce4(ph[0], ph[1], ph[2], ph[3]);
+              l2 = __builtin_amdgcn_logf(sm);
+              if (sm > kSumMax) l2 = kHighShift + __builtin_amdgcn_logf(sh);
+              if (__any(!(sm >= kSumMin && (sm <= kSumMax || (sh >= kSumMin && sh <= kSumMax))))) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                  const float lt = max_shifted_lse(z[t]);
+                  l2 = grp == t ? lt : l2;
+                }
+              }
+              if constexpr (V > 1) l2 = merge_sub_lse<V>(l2);
+            }
+            finish(IntTag<u>{}, l2);
           });
         });
         blk_next = blk_after;
-      }
-    };
-    auto run_each = [&](auto safe_tag) {
-#pragma unroll 1
-      for (int t = 0; t < n_steps; ++t) {
-        load_step(lane_block_clamped<V>(pt_row, first + 16 * t, n_c, lane));
-        run(first + 16 * t, IntTag<1>{}, safe_tag, 0);
       }
     };
     // with several steps a wave, the first step's records are on their way while the
@@ -304,14 +304,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
     QD = lane_digits(sDig, grp, col);
     if (n_steps == kSteps) {
       if (kSteps == 1) load_step(blk0);
-      run(first, IntTag<kSteps>{}, IntTag<0>{}, blk1);
+      run(first, IntTag<kSteps>{}, blk1);
     } else {
-      run_each(IntTag<0>{});
-    }
-    if (__any(bad)) {
-      run_m = -INFINITY;
-      run_s = 0.0f;
-      run_each(IntTag<1>{});
+#pragma unroll 1
+      for (int t = 0; t < n_steps; ++t) {
+        load_step(lane_block_clamped<V>(pt_row, first + 16 * t, n_c, lane));
+        run(first + 16 * t, IntTag<1>{}, 0);
+      }
     }
   }
   // ---- block partial (max, sum exp) per head over its pages, log2 domain: lane

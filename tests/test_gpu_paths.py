@@ -178,6 +178,39 @@ def test_rank8_scan_of_widely_spread_logits(G, page):
     _rank8_against_oracle(d, page, {(s, h) for s in (0, 1) for h in (0, 1)}, rtol=2e-6)
 
 
+@pytest.mark.parametrize("G,page", [(4, 16), (3, 32), (8, 64), (16, 16), (12, 64)])
+def test_rank8_scan_of_uncentred_coefficients(G, page):
+    """Records whose coefficient rows do not sum to zero: all of a page's logits may lie
+    hundreds of nats above or below its centroid's, where no sum of exponentials is in
+    float32's range without a shift.  Some pages keep their own rows."""
+    spec = WorkloadSpec("uncentred", 2, 2 * G, 2, [page * 70 + 1, page * 5], 8, page * 10, "bf16",
+                        "bf16", page_size=page)
+    d = Dev(build_workload(spec, 37))
+    d.w.q = (d.w.q.float() * 60).to(torch.bfloat16)
+    d.q = d.w.q.cuda()
+    store, recs = d.oracle_summaries()
+    out = torch.empty(2, 2 * G, d.cfg.max_pages_per_seq, device=d.device)
+    off = 64 * 8
+    for (s, h), rec in recs.items():
+        rec = rec.copy()
+        c = rec[:, off:off + 8 * page].reshape(-1, page, 8)
+        c[::3] = c[::3, :1]                       # every token the page's first row
+        rec[:, off:off + 8 * page] = c.reshape(rec.shape[0], -1)
+        recs[(s, h)] = rec
+        store[d.w.page_table[s, :rec.shape[0]].long().to(d.device), h] = torch.from_numpy(rec).to(d.device)
+    B.score_pages(d.cfg, d.q, store, d.pt, d.sl, d.ws, out)
+    torch.cuda.synchronize()
+    spread = 0.0
+    for (s, h), rec in recs.items():
+        k, v, qg = d.unit(s, h)
+        ref = O.decode_step(qg, k, v, rec, 8, d.cfg.budget_tokens, "int4", page)["s_hat"]
+        n_c = k.shape[0] // page
+        got = out[s, h * G:(h + 1) * G, :n_c].double().cpu().numpy()
+        np.testing.assert_allclose(got, ref[:, :n_c], atol=LSE_TOL, rtol=2e-6)
+        spread = max(spread, np.abs(ref).max())
+    assert spread > 100.0
+
+
 @pytest.mark.parametrize("G,rank,q", [(4, 8, "bf16"), (16, 8, "fp32"), (4, 2, "bf16")])
 def test_scores_with_an_unaligned_query(G, rank, q):
     """A query tensor that starts one element past a 16-byte boundary scores the same bits."""
