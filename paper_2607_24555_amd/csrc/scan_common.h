@@ -30,6 +30,7 @@ __device__ __forceinline__ int scan_chunk() {
 }
 
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 
@@ -183,29 +184,30 @@ __device__ __forceinline__ uint32_t rec_off(int b, uint32_t blk_bytes, uint32_t 
   return __umul24((uint32_t)b, blk_bytes) + head_off;
 }
 
-// Query digits of head gcol for the int8 projection: q is scaled by a power of
-// two to a 20-bit fixed-point integer Q (|Q| < 2^20) and split into three signed
-// 8-bit digits (most significant first).  Element e of MFMA half hh <-> d =
+// Query digits of a head for the int8 projection: q is scaled by a power of two to a
+// fixed-point integer Q and split into ND signed 8-bit digits (most significant first):
+// ND = 3, |Q| < 2^20, or ND = 4, |Q| < 2^30.  Element e of MFMA half hh <-> d =
 // 32 grp + 16 hh + perm16[e], the order in which the decoders expand the packed
 // codes.  bias[t] = -8 * sum(digit t) removes the excess-8 offset of the int4
 // codes.
 //
-// The digits are the bytes of U = Q + 0x808080 minus 128: U lies in [0, 2^24),
-// byte i of U is digit i + 128, and the lower two digits land in [-128, 127]
-// (the balanced base-256 digits of Q).  Four elements' bytes are gathered into
-// one digit word per digit by byte permutes, the +128 offsets flipped back by
-// one XOR, and each word's digit sum taken by one signed 4-way dot product.
+// The digits are the bytes of U = Q + 0x80808080 (three digits: its lower three) minus
+// 128: the lower digits land in [-128, 127] (the balanced base-256 digits of Q).  Four
+// elements' bytes are gathered into one digit word per digit by byte permutes, the +128
+// offsets flipped back by one XOR, and each word's digit sum taken by one signed 4-way dot
+// product.
+template <int ND>
 struct QDigits {
-  i4v bd[3][2];
-  int bias[3];
+  i4v bd[ND][2];
+  i4v bias;         // (a vector: as an array of four it was kept in LDS, 15 us a scan)
   float inv_scale;  // fixed-point unit * log2(e) / sqrt(d)
 };
 
 template <typename QT>
-__device__ __forceinline__ QDigits q_digits(const QT* __restrict__ qrow, int grp) {
+__device__ __forceinline__ QDigits<3> q_digits(const QT* __restrict__ qrow, int grp) {
   constexpr int kPerm16[16] = {0, 2, 4, 6, 1, 3, 5, 7, 8, 10, 12, 14, 9, 11, 13, 15};
   constexpr float c0 = 1.4426950408889634f * 0.08838834764831845f;  // log2(e) / sqrt(128)
-  QDigits D;
+  QDigits<3> D;
   float qf[32];
   float qmax = 0.0f;
 #pragma unroll
@@ -257,10 +259,10 @@ __device__ __forceinline__ QDigits q_digits(const QT* __restrict__ qrow, int grp
 // (each wave forming all of its lanes' digits itself took about 300 VALU instructions, a
 // tenth to a sixth of the wave's work).  Thread seg of a head holds elements 8 seg .. + 7:
 // half of the 16 bytes that lane group seg / 4 uses in MFMA half (seg / 2) % 2.
-template <int HG>
+template <int HG, int ND>
 struct DigitLds {
-  i4v bd[3][2][4][HG];  // [digit][half][lane group][head]
-  int bias[3][HG];
+  i4v bd[ND][2][4][HG];  // [digit][half][lane group][head]
+  int bias[ND][HG];
   float inv_scale[HG];
 };
 
@@ -294,43 +296,60 @@ __device__ __forceinline__ int dpp_i(int v) {
 }
 
 // Called by all 256 threads (q: the group's first row); a barrier must follow before the
-// digits are read.
-template <typename QT, int HG>
-__device__ __forceinline__ void block_digits(const QT* __restrict__ q, int G, DigitLds<HG>& S) {
+// digits are read.  With four digits a head whose query holds a NaN or an infinity gets a
+// NaN unit, so that all its scores are NaN.
+template <typename QT, int HG, int ND>
+__device__ __forceinline__ void block_digits(const QT* __restrict__ q, int G, DigitLds<HG, ND>& S) {
   constexpr float c0 = 1.4426950408889634f * 0.08838834764831845f;  // log2(e) / sqrt(128)
+  constexpr int kBits = ND == 4 ? 30 : 20;
   const int hd = threadIdx.x >> 4, seg = threadIdx.x & 15;
   if (hd >= HG) return;
   float x[8];
   load8_q(q + (hd < G ? hd : 0) * kDim + 8 * seg, x);
   float m = 0.0f;
+  bool finite = true;
+  if constexpr (ND == 4) {  // magnitudes compared as integers: infinities and NaN on top
+    uint32_t u = 0;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(x[e]));
-  m = fmaxf(m, __int_as_float(dpp_i<0xB1>(__float_as_int(m))));
-  m = fmaxf(m, __int_as_float(dpp_i<0x4E>(__float_as_int(m))));
-  m = fmaxf(m, __int_as_float(dpp_i<0x141>(__float_as_int(m))));
-  m = fmaxf(m, __int_as_float(dpp_i<0x140>(__float_as_int(m))));
+    for (int e = 0; e < 8; ++e) u = max(u, __float_as_uint(x[e]) & 0x7fffffffu);
+    u = max(u, (uint32_t)dpp_i<0xB1>((int)u));
+    u = max(u, (uint32_t)dpp_i<0x4E>((int)u));
+    u = max(u, (uint32_t)dpp_i<0x141>((int)u));
+    u = max(u, (uint32_t)dpp_i<0x140>((int)u));
+    finite = u < 0x7f800000u;
+    m = finite ? __uint_as_float(u) : 1.0f;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(x[e]));
+    m = fmaxf(m, __int_as_float(dpp_i<0xB1>(__float_as_int(m))));
+    m = fmaxf(m, __int_as_float(dpp_i<0x4E>(__float_as_int(m))));
+    m = fmaxf(m, __int_as_float(dpp_i<0x141>(__float_as_int(m))));
+    m = fmaxf(m, __int_as_float(dpp_i<0x140>(__float_as_int(m))));
+  }
   int ex = 0;
   (void)frexpf(m, &ex);  // m < 2^ex
-  const float qscale = ldexpf(1.0f, 20 - ex);
+  const float qscale = ldexpf(1.0f, kBits - ex);
+  constexpr int kMaxQ = (1 << kBits) - 1;
   uint32_t U[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const int Q = m > 0.0f ? min(max((int)rintf(x[e] * qscale), -0xFFFFF), 0xFFFFF) : 0;
-    U[e] = (uint32_t)(Q + 0x808080);
+    const int Q = m > 0.0f ? min(max((int)rintf(x[e] * qscale), -kMaxQ), kMaxQ) : 0;
+    U[e] = (uint32_t)Q + (ND == 4 ? 0x80808080u : 0x808080u);
   }
-  uint32_t w[3][2];  // [digit][even, odd elements]
+  uint32_t w[ND][2];  // [digit][even, odd elements]
 #pragma unroll
   for (int o = 0; o < 2; ++o) {
     const uint32_t lo01 = __builtin_amdgcn_perm(U[o + 2], U[o], 0x05010400u);
     const uint32_t lo23 = __builtin_amdgcn_perm(U[o + 6], U[o + 4], 0x05010400u);
     const uint32_t hi01 = __builtin_amdgcn_perm(U[o + 2], U[o], 0x07030602u);
     const uint32_t hi23 = __builtin_amdgcn_perm(U[o + 6], U[o + 4], 0x07030602u);
-    w[2][o] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u) ^ 0x80808080u;
-    w[1][o] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u) ^ 0x80808080u;
-    w[0][o] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u) ^ 0x80808080u;
+    w[ND - 1][o] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u) ^ 0x80808080u;
+    w[ND - 2][o] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u) ^ 0x80808080u;
+    w[ND - 3][o] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u) ^ 0x80808080u;
+    if (ND == 4) w[0][o] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u) ^ 0x80808080u;
   }
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
+  for (int d = 0; d < ND; ++d) {
     *reinterpret_cast<uint2*>(reinterpret_cast<uint32_t*>(&S.bd[d][(seg >> 1) & 1][seg >> 2][hd]) +
                               2 * (seg & 1)) = make_uint2(w[d][0], w[d][1]);
     int b = __builtin_amdgcn_sdot4((int)w[d][0], 0x01010101, 0, false);
@@ -341,21 +360,19 @@ __device__ __forceinline__ void block_digits(const QT* __restrict__ q, int G, Di
     b += dpp_i<0x140>(b);
     if (seg == 0) S.bias[d][hd] = -8 * b;
   }
-  if (seg == 0) S.inv_scale[hd] = ldexpf(1.0f, ex - 20) * c0;
+  if (seg == 0) S.inv_scale[hd] = finite ? ldexpf(1.0f, ex - kBits) * c0 : __int_as_float(0x7fc00000);
 }
 
 // Lane (grp, head)'s digits.
-template <int HG>
-__device__ __forceinline__ QDigits lane_digits(const DigitLds<HG>& S, int grp, int head) {
-  QDigits D;
+template <int HG, int ND>
+__device__ __forceinline__ void lane_digits(const DigitLds<HG, ND>& S, int grp, int head, QDigits<ND>& D) {
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
+  for (int d = 0; d < ND; ++d) {
     D.bd[d][0] = S.bd[d][0][grp][head];
     D.bd[d][1] = S.bd[d][1][grp][head];
     D.bias[d] = S.bias[d][head];
   }
   D.inv_scale = S.inv_scale[head];
-  return D;
 }
 
 // A 16-byte basis slice (32 excess-8 nibbles) as the int8 A operands of the two
@@ -374,7 +391,7 @@ __device__ __forceinline__ void nib_operands(const uint4& v, i4v (&a)[2]) {
 // a 20-bit query Q = 2^16 D0 + 2^8 D1 + D2, by Horner's rule over the digits in
 // one int32 accumulator: acc = 256 (256 (D0 . n') + D1 . n') + D2 . n'.  Every
 // partial value is bounded by |acc| <= 128 * 8 * 2^20 = 2^30, so nothing wraps.
-__device__ __forceinline__ i4v proj_horner(const i4v (&a)[2], const QDigits& QD) {
+__device__ __forceinline__ i4v proj_horner(const i4v (&a)[2], const QDigits<3>& QD) {
   i4v acc = i4v{QD.bias[0], QD.bias[0], QD.bias[0], QD.bias[0]};
   acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[0], QD.bd[0][0], acc, 0, 0, 0);
   acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[1], QD.bd[0][1], acc, 0, 0, 0);
@@ -390,9 +407,9 @@ __device__ __forceinline__ i4v proj_horner(const i4v (&a)[2], const QDigits& QD)
 }
 
 // Two independent projections by the same Horner steps, interleaved so that the
-// matrix-core work of one covers the shifts of the other.
-__device__ __forceinline__ void proj_horner2(const i4v (&a0)[2], const i4v (&a1)[2],
-                                             const QDigits& QD, i4v& r0, i4v& r1) {
+// matrix-core work of one covers the shifts of the other, in units of the query's scale.
+__device__ __forceinline__ void project2(const i4v (&a0)[2], const i4v (&a1)[2], const QDigits<3>& QD,
+                                         float (&p)[2][4]) {
   i4v x = i4v{QD.bias[0], QD.bias[0], QD.bias[0], QD.bias[0]};
   i4v y = x;
 #pragma unroll
@@ -408,8 +425,75 @@ __device__ __forceinline__ void proj_horner2(const i4v (&a0)[2], const i4v (&a1)
       for (int j = 0; j < 4; ++j) y[j] = (int)(((uint32_t)y[j] << 8) + (uint32_t)QD.bias[t + 1]);
     }
   }
-  r0 = x;
-  r1 = y;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) p[0][j] = (float)x[j];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) p[1][j] = (float)y[j];
+}
+// Four digits would leave int32 in one chain: two chains of two, upper and lower, joined as
+// floats.  The upper one, |x| <= 128 * 8 * 2^14, converts exactly, so p carries one float32
+// rounding of the sum and 2^-30 of the query's largest element per term.
+__device__ __forceinline__ void project2(const i4v (&a0)[2], const i4v (&a1)[2], const QDigits<4>& QD,
+                                         float (&p)[2][4]) {
+  const int b0 = QD.bias[0], b1 = QD.bias[1], b2 = QD.bias[2], b3 = QD.bias[3];
+  i4v x0 = {b0, b0, b0, b0}, y0 = {b2, b2, b2, b2}, x1 = x0, y1 = y0;
+  auto mac = [&](int hh, const i4v& dx, const i4v& dy) {
+    x0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0[hh], dx, x0, 0, 0, 0);
+    x1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1[hh], dx, x1, 0, 0, 0);
+    y0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0[hh], dy, y0, 0, 0, 0);
+    y1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1[hh], dy, y1, 0, 0, 0);
+  };
+  auto shift = [](i4v& v, int bias) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = (int)(((uint32_t)v[j] << 8) + (uint32_t)bias);
+  };
+  mac(0, QD.bd[0][0], QD.bd[2][0]);
+  mac(1, QD.bd[0][1], QD.bd[2][1]);
+  shift(x0, b1);
+  shift(x1, b1);
+  shift(y0, b3);
+  shift(y1, b3);
+  mac(0, QD.bd[1][0], QD.bd[3][0]);
+  mac(1, QD.bd[1][1], QD.bd[3][1]);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    p[0][j] = fmaf((float)x0[j], 65536.0f, (float)y0[j]);
+    p[1][j] = fmaf((float)x1[j], 65536.0f, (float)y1[j]);
+  }
+}
+
+// Integer dot product of a code row with Q from its dot products with the digits.
+__device__ __forceinline__ float join_digits(const int (&d)[3]) {
+  return fmaf((float)d[0], 65536.0f, (float)(d[1] * 256 + d[2]));
+}
+__device__ __forceinline__ float join_digits(const int (&d)[4]) {
+  return fmaf((float)(d[0] * 256 + d[1]), 65536.0f, (float)(d[2] * 256 + d[3]));
+}
+
+// The two upper halves of a pair of floats, as a pair of bfloat16 (truncation).
+__device__ __forceinline__ uint32_t top16(float a, float b) {
+  return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+}
+// Four excess-128 bytes -> four exact bfloat16 codes.
+__device__ __forceinline__ uint2 byte4_to_b4(uint32_t w) {
+  const uint32_t x = w ^ 0x80808080u;
+  float f[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) f[e] = (float)(int)(int8_t)(x >> (8 * e));
+  return make_uint2(top16(f[0], f[1]), top16(f[2], f[3]));
+}
+// A pair of floats as the sum of three pairs of bfloat16, exactly (8 bits of the 24 each;
+// no float is too large or too small, and NaN stays NaN).
+__device__ __forceinline__ void split3_b2(float a, float b, uint32_t (&t)[3]) {
+  auto cut = [](float v) { return __uint_as_float(__float_as_uint(v) & 0xffff0000u); };
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    t[i] = top16(a, b);
+    if (i < 2) {
+      a -= cut(a);
+      b -= cut(b);
+    }
+  }
 }
 
 template <int N>

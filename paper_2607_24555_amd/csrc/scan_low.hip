@@ -39,7 +39,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   __shared__ __align__(16) float sP[4][16][G][R];
   __shared__ float sA[4][16][G];
   __shared__ float2 sRun[4][64];
-  __shared__ DigitLds<G> sDig;  // query digits, shared by the waves
+  __shared__ DigitLds<G, 3> sDig;  // query digits, shared by the waves
 
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int col = lane & 15, grp = lane >> 4;
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   };
   // the query digits stay in LDS and are read at each use, leaving the registers to the
   // loads in flight
-  block_digits<QT, G>(q + row0 * kDim, G, sDig);
+  block_digits<QT, G, 3>(q + row0 * kDim, G, sDig);
   // the first step's records (the page-table load was in flight while the
   // digits were formed)
   uint4 ld[kLoads];

@@ -405,7 +405,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     FastRegs<R> cur;
     fast_issue<R>(cur, summ, pt_row, pg * 64, n_c, H_kv, h, lane);
 
-    const QDigits QD = q_digits(q + (row0 + gcol) * kDim, grp);
+    const QDigits<3> QD = q_digits(q + (row0 + gcol) * kDim, grp);
     const float inv_scale = QD.inv_scale;
     const i4v(&bd)[3][2] = QD.bd;
 

@@ -2,15 +2,17 @@
 // pages per wave step as four quads of 4 pages, no LDS in the step.
 //
 // The kernel is built for HG = 4 or 8 head columns; a group of G heads takes the
-// smaller HG >= G (columns g >= G repeat head 0 and are never stored).  Lane l =
+// smaller HG >= G (columns g >= G repeat head 0 and are never stored).  ND: query digits
+// (scan_digits).  Lane l =
 // (grp = l / 16, col = l % 16); col = (cb, g) = (col / HG, col % HG).
 //
 // For quad Q of a step:
 //  * stage 1 (int8 MFMA, two basis sets i = 0, 1): A row m is (page 4 Q + m / 4, basis
 //    column 4 i + m % 4); the 16 B columns are the HG heads repeated 16 / HG times.
 //    Lane (grp, col) receives p(page 4 Q + grp, l = 4 i + j, head g) in register j.
-//  * stage 2 (f16 MFMA 16x16x32, B as hi + lo): rows are the 16 tokens, K index 8 a + l
-//    is (page 4 Q + a, basis column l), columns are (page, head).  HG columns leave
+//  * stage 2 (16x16x32 MFMA, B as float16 hi + lo or, with four query digits, as three
+//    bfloat16 terms): rows are the 16 tokens, K index 8 a + l is (page 4 Q + a, basis column
+//    l), columns are (page, head).  HG columns leave
 //    room for kCP = 16 / HG pages, so a quad takes kNP = HG / 4 passes; pass t covers
 //    pages kCP t + cb.  A lane's 8 stage-1 values enter where the column's page is the
 //    lane's own (grp % kCP == cb, by a zero scale elsewhere), and the A rows of the
@@ -35,9 +37,9 @@
 // Bound: at 16-token pages the scattered record gather (8 x 128K, four-head groups: 94 us,
 // 4.6 TB/s, where the gather alone runs at 5.2 to 5.7); at 32 and 64 tokens the vector
 // ALU's work per sub-page, so the per-step tail above is shared by the quads and the
-// instances of four columns are held to 168 registers (three waves per SIMD; at two, 32-token
-// pages take 52 us for 46): 8 x 128K in 64-token pages 38.5 us.  Those of eight columns take
-// 197 to 229 registers, two waves.
+// instances for groups of four are held to 168 registers (three waves per SIMD; at two, 32-token
+// pages take 52 us for 46): 8 x 128K in 64-token pages 38.5 us.  The others' four-step
+// instances take 189 to 246 registers, two waves.
 #pragma once
 
 #include "locks_internal.h"
@@ -61,8 +63,8 @@ __device__ __forceinline__ float row_xor(float v) {
   return __int_as_float(u);
 }
 
-template <typename QT, int HG, int kSteps, int V>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 4 && V > 1 ? 3 : 2))) void scan_quad_kernel(
+template <typename QT, int HG, int ND, int kSteps, int V>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 4 && ND == 3 && V > 1 ? 3 : 2))) void scan_quad_kernel(
     int H_q, int H_kv, int G, int max_pages, const QT* __restrict__ q,
     const uint8_t* __restrict__ summ, uint32_t summ_bytes, const int32_t* __restrict__ page_table,
     const int32_t* __restrict__ seq_lens, float* __restrict__ s_hat, SHatLayout lay,
@@ -72,7 +74,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 4 && 
   constexpr uint32_t kStride = rec_stride(R, 0, P);
   constexpr uint32_t kCoef = rec_coef_off(R), kMu = rec_mu_off(R, 0, P), kSc = rec_scale_off(R, 0, P);
   __shared__ float2 sRun[4][16];
-  __shared__ DigitLds<HG> sDig;
+  __shared__ DigitLds<HG, ND> sDig;
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int col = lane & 15, grp = lane >> 4;
@@ -96,7 +98,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 4 && 
   const bool has = first < n_c;  // pages for this wave
   {
     const int n_steps = has ? min(kSteps, (n_c - first + 15) / 16) : 0;
-    QDigits QD;          // read from the block's once formed
+    QDigits<ND> QD;      // read from the block's once formed
     float inv_m = 0.0f;  // scale of the stage-1 values; zero where the page is not the column's
     // own(u): the u-th page of the step (0 .. 15) whose score this lane finishes
     auto own = [&](int u) { return HG == 4 ? 4 * grp + cb : 4 * grp + 2 * u + cb; };
@@ -205,9 +207,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 4 && 
                                   mu[1].x ^ 0x80808080u, mu[1].y ^ 0x80808080u,
                                   mu[1].z ^ 0x80808080u, mu[1].w ^ 0x80808080u};
           if (pf) ld_mu(on);
-          i4v acc[3];
+          i4v acc[ND];
 #pragma unroll
-          for (int d = 0; d < 3; ++d) acc[d] = i4v{0, 0, 0, 0};
+          for (int d = 0; d < ND; ++d) acc[d] = i4v{0, 0, 0, 0};
 #pragma unroll
           for (int hh = 0; hh < 2; ++hh) {
             const uint32_t y0 = mw[4 * hh], y1 = mw[4 * hh + 1], y2 = mw[4 * hh + 2], y3 = mw[4 * hh + 3];
@@ -216,24 +218,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 4 && 
                            (int)__builtin_amdgcn_perm(y3, y2, 0x06040200u),
                            (int)__builtin_amdgcn_perm(y3, y2, 0x07050301u)};
 #pragma unroll
-            for (int d = 0; d < 3; ++d)
+            for (int d = 0; d < ND; ++d)
               acc[d] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, QD.bd[d][hh], acc[d], 0, 0, 0);
           }
-          int da[kNP][3];
 #pragma unroll
-          for (int u = 0; u < kNP; ++u)
+          for (int u = 0; u < kNP; ++u) {
+            int da[ND];
 #pragma unroll
-            for (int d = 0; d < 3; ++d) {
+            for (int d = 0; d < ND; ++d) {
               if constexpr (HG == 8) {
-                da[u][d] = cb ? acc[d][2 * u + 1] : acc[d][2 * u];
+                da[d] = cb ? acc[d][2 * u + 1] : acc[d][2 * u];
               } else {
                 const int lo = (cb & 1) ? acc[d][1] : acc[d][0], hi = (cb & 1) ? acc[d][3] : acc[d][2];
-                da[u][d] = (cb & 2) ? hi : lo;
+                da[d] = (cb & 2) ? hi : lo;
               }
             }
-#pragma unroll
-          for (int u = 0; u < kNP; ++u)
-            am[u] = fmaf((float)da[u][0], 65536.0f, (float)(da[u][1] * 256 + da[u][2]));
+            am[u] = join_digits(da);
+          }
         }
 
         float bq[kShare][8];  // shared stage 1: the values of the step's quads
@@ -259,12 +260,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 4 && 
           float vals[8];
           if (Q % kShare == 0) {
             const int m = Q / kShare;
-            i4v acc1[2];
+            float p[2][4];
             {
               i4v a0[2], a1[2];
               nib_operands(vb[m][0], a0);
               nib_operands(vb[m][1], a1);
-              proj_horner2(a0, a1, QD, acc1[0], acc1[1]);
+              project2(a0, a1, QD, p);
               if (pf) {
                 ld_vb(on, m, 0);
                 ld_vb(on, m, 1);
@@ -277,7 +278,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 4 && 
               const int j = l & 3;
               const h2 pr = as_h2(vsw[l >> 1]);
               const float vsc = (float)((l & 1) ? pr.y : pr.x);
-              vals[l] = (float)acc1[l >> 2][j] * (vsc * sc);
+              vals[l] = p[l >> 2][j] * (vsc * sc);
             }
             if (pf) ld_vs(on, m);
             if constexpr (kShare > 1) {
@@ -308,18 +309,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 4 && 
 #pragma unroll
             for (int l = 0; l < 8; ++l) vals[l] = mine ? bq[Q % kShare][l] : 0.0f;
           }
-          const uint4 A = __builtin_bit_cast(uint4, byte8_to_h8(cf[Q].x, cf[Q].y));
+          uint4 A;
+          if constexpr (ND == 3) {
+            A = __builtin_bit_cast(uint4, byte8_to_h8(cf[Q].x, cf[Q].y));
+          } else {
+            const uint2 a0 = byte4_to_b4(cf[Q].x), a1 = byte4_to_b4(cf[Q].y);
+            A = make_uint4(a0.x, a0.y, a1.x, a1.y);
+          }
           if (pf) ld_cf(on, Q);
           // ---- stage 2 for the quad
-          h8 bh, bl;
+          uint32_t bt[ND - 1][4];  // the terms of B
 #pragma unroll
-          for (int e = 0; e < 8; e += 2) {
-            const auto hi = __builtin_amdgcn_cvt_pkrtz(vals[e], vals[e + 1]);
-            const auto lo = __builtin_amdgcn_cvt_pkrtz(vals[e] - (float)hi[0], vals[e + 1] - (float)hi[1]);
-            bh[e] = hi[0];
-            bh[e + 1] = hi[1];
-            bl[e] = lo[0];
-            bl[e + 1] = lo[1];
+          for (int e = 0; e < 4; ++e) {
+            if constexpr (ND == 3) {
+              const auto hi = __builtin_amdgcn_cvt_pkrtz(vals[2 * e], vals[2 * e + 1]);
+              const auto lo = __builtin_amdgcn_cvt_pkrtz(vals[2 * e] - (float)hi[0], vals[2 * e + 1] - (float)hi[1]);
+              bt[0][e] = __builtin_bit_cast(uint32_t, hi);
+              bt[1][e] = __builtin_bit_cast(uint32_t, lo);
+            } else {
+              uint32_t t3[3];
+              split3_b2(vals[2 * e], vals[2 * e + 1], t3);
+#pragma unroll
+              for (int i = 0; i < 3; ++i) bt[i][e] = t3[i];
+            }
           }
           float z[kNP][4];
           uint64_t far = force;  // lanes whose sum is too large
@@ -331,8 +343,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 4 && 
               At = make_uint4(in ? A.x : 0u, in ? A.y : 0u, in ? A.z : 0u, in ? A.w : 0u);
             }
             f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, At), bh, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, At), bl, acc, 0, 0, 0);
+#pragma unroll
+            for (int i = ND - 2; i >= 0; --i) {  // smallest terms first
+              const uint4 Bt = make_uint4(bt[i][0], bt[i][1], bt[i][2], bt[i][3]);
+              if constexpr (ND == 3)
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, At),
+                                                             __builtin_bit_cast(h8, Bt), acc, 0, 0, 0);
+              else
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(b8, At),
+                                                              __builtin_bit_cast(b8, Bt), acc, 0, 0, 0);
+            }
             const h2 c01 = as_h2(cs[Q][t].x), c23 = as_h2(cs[Q][t].y);
             z[t][0] = (float)c01.x * acc[0];
             z[t][1] = (float)c01.y * acc[1];
@@ -399,9 +419,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 4 && 
       blk1 = kSteps > 1 ? lane_block_clamped<V>(pt_row, first + 16, n_c, lane) : 0;
       if (kSteps > 1) load_step(blk0);
     }
-    block_digits<QT, HG>(q + row0 * kDim, G, sDig);
+    block_digits<QT, HG, ND>(q + row0 * kDim, G, sDig);
     __syncthreads();
-    QD = lane_digits(sDig, grp, g);
+    lane_digits(sDig, grp, g, QD);
     inv_m = mine ? QD.inv_scale : 0.0f;
     if (n_steps == kSteps) {
       if (kSteps == 1) load_step(blk0);
@@ -442,16 +462,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 4 && 
 
 template <typename QT>
 hipError_t launch_scan_quad(const ScanArgs& a, int hg, int steps, int v, hipStream_t st) {
-#define LOCKS_QUAD(HH, SS, VV)                                                                \
-  if (hg == HH && steps == SS && v == VV) {                                                   \
-    hipLaunchKernelGGL((scan_quad_kernel<QT, HH, SS, VV>), a.grid, dim3(256), 0, st, a.H_q,   \
-                       a.H_kv, a.H_q / a.H_kv, a.max_pages, static_cast<const QT*>(a.q),      \
-                       a.summ, a.summ_bytes, a.page_table, a.seq_lens, a.s_hat, a.lay,        \
-                       a.partials);                                                           \
+  const int nd = scan_digits(a.H_q / a.H_kv);
+#define LOCKS_QUAD(HH, ND, SS, VV)                                                            \
+  if (hg == HH && nd == ND && steps == SS && v == VV) {                                       \
+    hipLaunchKernelGGL((scan_quad_kernel<QT, HH, ND, SS, VV>), a.grid, dim3(256), 0, st,      \
+                       a.H_q, a.H_kv, a.H_q / a.H_kv, a.max_pages,                            \
+                       static_cast<const QT*>(a.q), a.summ, a.summ_bytes, a.page_table,       \
+                       a.seq_lens, a.s_hat, a.lay, a.partials);                               \
     return hipGetLastError();                                                                 \
   }
-#define LOCKS_QUAD_V(HH, SS) LOCKS_QUAD(HH, SS, 1) LOCKS_QUAD(HH, SS, 2) LOCKS_QUAD(HH, SS, 4)
-  LOCKS_QUAD_V(4, 1) LOCKS_QUAD_V(4, 4) LOCKS_QUAD_V(8, 1) LOCKS_QUAD_V(8, 4)
+#define LOCKS_QUAD_V(HH, ND, SS) LOCKS_QUAD(HH, ND, SS, 1) LOCKS_QUAD(HH, ND, SS, 2) LOCKS_QUAD(HH, ND, SS, 4)
+  LOCKS_QUAD_V(4, 3, 1) LOCKS_QUAD_V(4, 3, 4) LOCKS_QUAD_V(4, 4, 1) LOCKS_QUAD_V(4, 4, 4)
+  LOCKS_QUAD_V(8, 4, 1) LOCKS_QUAD_V(8, 4, 4)
 #undef LOCKS_QUAD_V
 #undef LOCKS_QUAD
   return launch_scan_wide<QT>(a, steps, v, st);

@@ -9,7 +9,8 @@
 //    B operand of a 16x16x16 f16 MFMA for each of the two pages: K rows 0..7 hold hi of
 //    l = 0..7, rows 8..15 lo.  Its A operand is the token's coefficient row twice, a
 //    4-byte load whose record offset is wave-uniform.  So stage 2 takes one MFMA per
-//    16 tokens with no zeros in it.
+//    16 tokens with no zeros in it.  (With four query digits, ND of scan_digits: three
+//    bfloat16 terms, the third in an MFMA of its own.)
 //  * Register j of lane (grp, col) is the logit of token 4 grp + j for head col, minus
 //    the centroid logit.  The sums of 2^z over a lane's 4 tokens are reduced over grp
 //    four (sub-)pages at a time, the totals handed to the four lane rows (reduce4): row
@@ -36,8 +37,9 @@ namespace locks {
 namespace {
 
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+typedef short s4 __attribute__((ext_vector_type(4)));
 
-template <typename QT, int kSteps, int V>
+template <typename QT, int ND, int kSteps, int V>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void scan_wide_kernel(
     int H_q, int H_kv, int G, int max_pages, const QT* __restrict__ q,
     const uint8_t* __restrict__ summ, uint32_t summ_bytes, const int32_t* __restrict__ page_table,
@@ -49,7 +51,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
   constexpr uint32_t kStride = rec_stride(R, 0, P);
   constexpr uint32_t kCoef = rec_coef_off(R), kMu = rec_mu_off(R, 0, P), kSc = rec_scale_off(R, 0, P);
   __shared__ float2 sRun[4][16];
-  __shared__ DigitLds<16> sDig;
+  __shared__ DigitLds<16, ND> sDig;
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int col = lane & 15, grp = lane >> 4;
@@ -70,7 +72,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
   const bool has = first < n_c;  // pages for this wave
   {
     const int n_steps = has ? min(kSteps, (n_c - first + 15) / 16) : 0;
-    QDigits QD;  // read from the block's once formed
+    QDigits<ND> QD;  // read from the block's once formed
     float* shat_lane = s_hat + lay.base(s, h) + (long)col * lay.head;
 
     // record offsets of one step: va[m][i] page 4 m + 2 i + col / 8 (stage-1 rows),
@@ -159,9 +161,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
                                   mu[1].x ^ 0x80808080u, mu[1].y ^ 0x80808080u,
                                   mu[1].z ^ 0x80808080u, mu[1].w ^ 0x80808080u};
           if (pf) ld_mu(on);
-          i4v acc[3];
+          i4v acc[ND];
 #pragma unroll
-          for (int d = 0; d < 3; ++d) acc[d] = i4v{0, 0, 0, 0};
+          for (int d = 0; d < ND; ++d) acc[d] = i4v{0, 0, 0, 0};
 #pragma unroll
           for (int hh = 0; hh < 2; ++hh) {
             const uint32_t y0 = mw[4 * hh], y1 = mw[4 * hh + 1], y2 = mw[4 * hh + 2], y3 = mw[4 * hh + 3];
@@ -170,12 +172,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
                            (int)__builtin_amdgcn_perm(y3, y2, 0x06040200u),
                            (int)__builtin_amdgcn_perm(y3, y2, 0x07050301u)};
 #pragma unroll
-            for (int d = 0; d < 3; ++d)
+            for (int d = 0; d < ND; ++d)
               acc[d] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, QD.bd[d][hh], acc[d], 0, 0, 0);
           }
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            am[j] = fmaf((float)acc[0][j], 65536.0f, (float)(acc[1][j] * 256 + acc[2][j]));
+          for (int j = 0; j < 4; ++j) {
+            int da[ND];
+#pragma unroll
+            for (int d = 0; d < ND; ++d) da[d] = acc[d][j];
+            am[j] = join_digits(da);
+          }
         }
         // the step's row scales in fp32 and centroid scales x the query scale's unit,
         // in the lanes that loaded them
@@ -205,38 +211,52 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
         static_for_int<kPairs>([&](auto m_tag) __attribute__((always_inline)) {
           constexpr int m = decltype(m_tag)::value;
           __builtin_amdgcn_sched_barrier(0);
-          i4v acc1[2];
+          float p[2][4];
           {
             i4v a0[2], a1[2];
             nib_operands(vb[m][0], a0);
             nib_operands(vb[m][1], a1);
-            proj_horner2(a0, a1, QD, acc1[0], acc1[1]);
+            project2(a0, a1, QD, p);
             if (pf) {
               ld_vb(on, m, 0);
               ld_vb(on, m, 1);
             }
           }
-          // B operands of the pair's four pages
-          h4 bp[4];
+          // B operands of the pair's four pages: K rows 0..7 the first term, 8..15 the
+          // second; with a third term, another operand of it and zeros
+          constexpr int kOps = ND == 3 ? 1 : 2;
+          uint2 bp[4][kOps];
 #pragma unroll
           for (int i = 0; i < 2; ++i) {
             const h2 s01 = as_h2(vs[m][i].x), s23 = as_h2(vs[m][i].y);
             const float sc[4] = {(float)s01.x, (float)s01.y, (float)s23.x, (float)s23.y};
             if (pf) ld_vs(on, m, i);
-            uint32_t hi[2], lo[2];
+            uint32_t bt[2][2 * kOps];  // [pair of columns][term]
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
-              const float x = (float)acc1[i][2 * e] * (sc[2 * e] * QD.inv_scale);
-              const float y = (float)acc1[i][2 * e + 1] * (sc[2 * e + 1] * QD.inv_scale);
-              const auto hp = __builtin_amdgcn_cvt_pkrtz(x, y);
-              const auto lp = __builtin_amdgcn_cvt_pkrtz(x - (float)hp[0], y - (float)hp[1]);
-              hi[e] = __builtin_bit_cast(uint32_t, hp);
-              lo[e] = __builtin_bit_cast(uint32_t, lp);
+              const float x = p[i][2 * e] * (sc[2 * e] * QD.inv_scale);
+              const float y = p[i][2 * e + 1] * (sc[2 * e + 1] * QD.inv_scale);
+              if constexpr (ND == 3) {
+                const auto hp = __builtin_amdgcn_cvt_pkrtz(x, y);
+                const auto lp = __builtin_amdgcn_cvt_pkrtz(x - (float)hp[0], y - (float)hp[1]);
+                bt[e][0] = __builtin_bit_cast(uint32_t, hp);
+                bt[e][1] = __builtin_bit_cast(uint32_t, lp);
+              } else {
+                uint32_t t3[3];
+                split3_b2(x, y, t3);
+                bt[e][0] = t3[0];
+                bt[e][1] = t3[1];
+                bt[e][2] = t3[2];
+                bt[e][3] = 0u;
+              }
             }
-            const auto w0 = __builtin_amdgcn_permlane32_swap(hi[0], lo[0], false, false);
-            const auto w1 = __builtin_amdgcn_permlane32_swap(hi[1], lo[1], false, false);
-            bp[2 * i] = __builtin_bit_cast(h4, make_uint2(w0[0], w1[0]));
-            bp[2 * i + 1] = __builtin_bit_cast(h4, make_uint2(w0[1], w1[1]));
+#pragma unroll
+            for (int o = 0; o < kOps; ++o) {
+              const auto w0 = __builtin_amdgcn_permlane32_swap(bt[0][2 * o], bt[0][2 * o + 1], false, false);
+              const auto w1 = __builtin_amdgcn_permlane32_swap(bt[1][2 * o], bt[1][2 * o + 1], false, false);
+              bp[2 * i][o] = make_uint2(w0[0], w1[0]);
+              bp[2 * i + 1][o] = make_uint2(w0[1], w1[1]);
+            }
           }
           // V quads of (sub-)pages: quad Qv covers sub-pages 4 Qv .. of the pair
           static_for_int<V>([&](auto v_tag) __attribute__((always_inline)) {
@@ -246,12 +266,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
               constexpr int t = decltype(t_tag)::value, sp = 4 * u + t;
               const uint32_t w = cf[sp];
               if (pf) ld_cf(on, sp);
-              const h2 k{(_Float16)1152.0f, (_Float16)1152.0f};
-              const h2 a01 = as_h2(__builtin_amdgcn_perm(0x64646464u, w, 0x04010400u)) - k;
-              const h2 a23 = as_h2(__builtin_amdgcn_perm(0x64646464u, w, 0x04030402u)) - k;
-              const h4 A{a01.x, a01.y, a23.x, a23.y};
               f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-              acc = __builtin_amdgcn_mfma_f32_16x16x16f16(A, bp[(4 * Qv + t) / V], acc, 0, 0, 0);
+              const auto& B = bp[(4 * Qv + t) / V];
+              if constexpr (ND == 3) {
+                const h2 k{(_Float16)1152.0f, (_Float16)1152.0f};
+                const h2 a01 = as_h2(__builtin_amdgcn_perm(0x64646464u, w, 0x04010400u)) - k;
+                const h2 a23 = as_h2(__builtin_amdgcn_perm(0x64646464u, w, 0x04030402u)) - k;
+                const h4 A{a01.x, a01.y, a23.x, a23.y};
+                acc = __builtin_amdgcn_mfma_f32_16x16x16f16(A, __builtin_bit_cast(h4, B[0]), acc, 0, 0, 0);
+              } else {
+                const s4 A = __builtin_bit_cast(s4, byte4_to_b4(w));
+                acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A, __builtin_bit_cast(s4, B[kOps - 1]), acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A, __builtin_bit_cast(s4, B[0]), acc, 0, 0, 0);
+              }
 #pragma unroll
               for (int j = 0; j < 4; ++j) z[t][j] = row_bcast<sp>(csf[j]) * acc[j];
               ps[t] = (__builtin_amdgcn_exp2f(z[t][0]) + __builtin_amdgcn_exp2f(z[t][1])) +
@@ -299,9 +326,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
       blk1 = kSteps > 1 ? lane_block_clamped<V>(pt_row, first + 16, n_c, lane) : 0;
       if (kSteps > 1) load_step(blk0);
     }
-    block_digits<QT, 16>(q + row0 * kDim, G, sDig);
+    block_digits<QT, 16, ND>(q + row0 * kDim, G, sDig);
     __syncthreads();
-    QD = lane_digits(sDig, grp, col);
+    lane_digits(sDig, grp, col, QD);
     if (n_steps == kSteps) {
       if (kSteps == 1) load_step(blk0);
       run(first, IntTag<kSteps>{}, blk1);
@@ -335,15 +362,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
 
 template <typename QT>
 hipError_t launch_scan_wide(const ScanArgs& a, int steps, int v, hipStream_t st) {
-#define LOCKS_WIDE(SS, VV)                                                                    \
-  if (steps == SS && v == VV) {                                                               \
-    hipLaunchKernelGGL((scan_wide_kernel<QT, SS, VV>), a.grid, dim3(256), 0, st, a.H_q,       \
+  const int nd = scan_digits(a.H_q / a.H_kv);
+#define LOCKS_WIDE(ND, SS, VV)                                                                \
+  if (nd == ND && steps == SS && v == VV) {                                                   \
+    hipLaunchKernelGGL((scan_wide_kernel<QT, ND, SS, VV>), a.grid, dim3(256), 0, st, a.H_q,   \
                        a.H_kv, a.H_q / a.H_kv, a.max_pages, static_cast<const QT*>(a.q),      \
                        a.summ, a.summ_bytes, a.page_table, a.seq_lens, a.s_hat, a.lay,        \
                        a.partials);                                                           \
     return hipGetLastError();                                                                 \
   }
-  LOCKS_WIDE(1, 1) LOCKS_WIDE(4, 1) LOCKS_WIDE(1, 2) LOCKS_WIDE(4, 2) LOCKS_WIDE(1, 4) LOCKS_WIDE(4, 4)
+#define LOCKS_WIDE_V(ND, SS) LOCKS_WIDE(ND, SS, 1) LOCKS_WIDE(ND, SS, 2) LOCKS_WIDE(ND, SS, 4)
+  LOCKS_WIDE_V(3, 1) LOCKS_WIDE_V(3, 4) LOCKS_WIDE_V(4, 1) LOCKS_WIDE_V(4, 4)
+#undef LOCKS_WIDE_V
 #undef LOCKS_WIDE
   return hipErrorInvalidValue;
 }

@@ -211,6 +211,97 @@ def test_rank8_scan_of_uncentred_coefficients(G, page):
     assert spread > 100.0
 
 
+def _rank8_scores(G, page, q_dtype, edit, seed=41):
+    """Page scores of rank-8 units and their 64-bit values, after edit(workload) changed
+    its tensors."""
+    spec = WorkloadSpec("digits", 2, 2 * G, 2, [page * 70 + 1, page * 5], 8, page * 10, "bf16",
+                        q_dtype, page_size=page)
+    w = build_workload(spec, seed)
+    edit(w)
+    d = Dev(w)
+    store, recs = d.oracle_summaries()
+    out = B.score_pages(d.cfg, d.q, store, d.pt, d.sl, d.ws)
+    torch.cuda.synchronize()
+    got, want = [], []
+    for (s, h), rec in recs.items():
+        k, v, qg = d.unit(s, h)
+        n_c = k.shape[0] // page
+        got.append(out[s, h * G:(h + 1) * G, :n_c].double().cpu().numpy())
+        with np.errstate(invalid="ignore"):           # queries that are not finite
+            ref = O.decode_step(qg, k, v, rec, 8, d.cfg.budget_tokens, "int4", page)
+        want.append(ref["s_hat"][:, :n_c])
+    return got, want
+
+
+# every head-column width of the rank-8 scans, without the four- and sixteen-head groups
+# (whose queries are held in 20 bits of the head's largest element)
+WIDE_QUERY = [(1, 16, "fp32"), (3, 16, "bf16"), (2, 32, "fp32"), (3, 64, "bf16"), (8, 16, "bf16"),
+              (7, 16, "fp32"), (5, 32, "bf16"), (6, 64, "fp32"), (9, 16, "fp32"), (15, 32, "bf16"),
+              (12, 64, "fp32")]
+
+
+@pytest.mark.parametrize("G,page,q", WIDE_QUERY)
+def test_scores_of_a_query_with_a_dominant_channel(G, page, q):
+    """One query channel 1,000 times the others, on which the keys are zero: the scores rest
+    on elements 2^-13 of the largest.  Held: 2^-31 of the largest element (8 x 1,024) per
+    channel, over 127 channels of keys of up to 16, over sqrt(128), and the roundings of
+    scores of up to 100."""
+    def edit(w):
+        w.k_cache[..., 0] = 0
+        w.q[..., 0] = 1024.0 * w.q.float().abs().amax(-1).clamp(max=8.0).to(w.q.dtype)
+    got, want = _rank8_scores(G, page, q, edit)
+    tol = 2.0 ** -31 * 8192 * 16 * 127 / 128 ** 0.5 + 2.0 ** -21 * 100
+    err = max(np.abs(a - b).max() for a, b in zip(got, want))
+    assert np.abs(want[0]).max() <= 100
+    assert err <= tol, (err, tol)
+
+
+@pytest.mark.parametrize("G,page", [(g, p) for g, p, q in WIDE_QUERY if q == "fp32"])
+def test_scores_of_fp32_queries_keep_float32(G, page):
+    """fp32 queries that bf16 does not hold: the mean error over the pages is within half a
+    unit in the last place of the largest score, which the roundings of the score's own
+    sums (a handful, of either sign) leave on average."""
+    def edit(w):
+        gen = torch.Generator().manual_seed(3)
+        w.q *= 1 + 0.01 * torch.rand(w.q.shape, generator=gen)
+    got, want = _rank8_scores(G, page, "fp32", edit)
+    err = np.concatenate([np.abs(a - b).ravel() for a, b in zip(got, want)])
+    top = max(np.abs(b).max() for b in want)
+    print(f"[paths fp32 queries] G={G} page={page}: mean {err.mean():.2e} max {err.max():.2e} of {top:.1f}")
+    assert err.mean() <= 2.0 ** -24 * top, (err.mean(), top)
+
+
+@pytest.mark.parametrize("G,page,q", WIDE_QUERY)
+def test_scores_of_huge_queries(G, page, q):
+    """Queries of 1e6 (projections past float16's range): scores stay relative to float32."""
+    def edit(w):
+        w.q = (w.q.float() * 1e6).to(w.q.dtype)
+    got, want = _rank8_scores(G, page, q, edit)
+    for a, b in zip(got, want):
+        np.testing.assert_allclose(a, b, rtol=0, atol=2.0 ** -21 * max(np.abs(x).max() for x in want))
+
+
+@pytest.mark.parametrize("G,page,q", WIDE_QUERY)
+def test_scores_of_a_query_that_is_not_finite(G, page, q):
+    """A NaN or an infinity in a head's query makes that head's scores NaN and leaves the
+    other heads' as they are, up to the rounding of sums that are then taken with their max
+    shifted out (four units in the last place)."""
+    base, _ = _rank8_scores(G, page, q, lambda w: None)
+
+    def edit(w):
+        w.q[0, 0, 5] = float("nan")
+        w.q[0, G + G // 2, 127] = float("-inf")
+    got, _ = _rank8_scores(G, page, q, edit)
+    bad = {(0, 0), (1, G // 2)}                       # (KV head, head of its group) of sequence 0
+    for i, (a, b) in enumerate(zip(got, base)):
+        s, h = divmod(i, 2)
+        for g in range(G):
+            if s == 0 and (h, g) in bad:
+                assert np.isnan(a[g]).all()
+            else:
+                np.testing.assert_allclose(a[g], b[g], rtol=2.0 ** -21, atol=0)
+
+
 @pytest.mark.parametrize("G,rank,q", [(4, 8, "bf16"), (16, 8, "fp32"), (4, 2, "bf16")])
 def test_scores_with_an_unaligned_query(G, rank, q):
     """A query tensor that starts one element past a 16-byte boundary scores the same bits."""
