@@ -179,9 +179,11 @@ __device__ __forceinline__ uint32_t bld4(__amdgpu_buffer_rsrc_t r, uint32_t off,
   return __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, 0);
 }
 // Byte offset of the record of (physical block b, KV head h): b * (H_kv * stride)
-// + h * stride, with a 24-bit multiply (b < 2^24, the store is below 4 GiB).
+// + h * stride.  32 bits hold it, as the store is below 4 GiB; a 24-bit multiply would not
+// do, as a block's records pass 2^24 bytes from 20,165 KV heads on (832-byte records).  The
+// full multiply runs once per lane and 16-page step.
 __device__ __forceinline__ uint32_t rec_off(int b, uint32_t blk_bytes, uint32_t head_off) {
-  return __umul24((uint32_t)b, blk_bytes) + head_off;
+  return (uint32_t)b * blk_bytes + head_off;
 }
 
 // Query digits of a head for the int8 projection: q is scaled by a power of two to a

@@ -61,9 +61,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 
   const __amdgpu_buffer_rsrc_t rs = summ_rsrc(summ, summ_bytes);
   const uint32_t blk_bytes = (uint32_t)H_kv * kStride, head_off = (uint32_t)h * kStride;
-  // blocks of the wave's 64 pages, page first + l in lane l (pages past the end
+  // record offsets of the wave's 64 pages, page first + l in lane l (pages past the end
   // repeat the last complete one)
-  const int blk_all = has ? pt_row[min(first + lane, n_c - 1)] : 0;
+  const int off_all =
+      (int)rec_off(has ? pt_row[min(first + lane, n_c - 1)] : 0, blk_bytes, head_off);
   // chunk c = lane + 64 u of step t is chunk c % kCh of page 16 t + c / kCh; it
   // lands at byte 16 c of the wave's LDS slot
   auto issue = [&](int t, uint4 (&ld)[kLoads]) {
@@ -71,8 +72,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     for (int u = 0; u < kLoads; ++u) {
       int c = lane + 64 * u;
       c = c < 16 * kCh ? c : 16 * kCh - 1;
-      const int b = __shfl(blk_all, 16 * t + c / kCh, 64);
-      ld[u] = bld16(rs, rec_off(b, blk_bytes, head_off) + (c % kCh) * 16);
+      const uint32_t off = (uint32_t)__shfl(off_all, 16 * t + c / kCh, 64);
+      ld[u] = bld16(rs, off + (c % kCh) * 16);
     }
   };
   // the query digits stay in LDS and are read at each use, leaving the registers to the

@@ -302,6 +302,29 @@ def test_scores_of_a_query_that_is_not_finite(G, page, q):
                 np.testing.assert_allclose(a[g], b[g], rtol=2.0 ** -21, atol=0)
 
 
+@pytest.mark.parametrize("G,rank,heads", [(1, 8, 20480), (9, 8, 20480), (4, 2, 50048)])
+def test_scores_of_blocks_past_16_mib(G, rank, heads):
+    """So many KV heads that one block's records pass 2^24 bytes: each head's scores equal
+    those of the same head in a store of 64 heads (the same records, the same sums)."""
+    cfg = B.Config(1, 64 * G, 64, rank, 256, 4, 4)
+    gen = torch.Generator().manual_seed(11)
+    k = torch.randn(4, 64, 16, 128, generator=gen).to(torch.bfloat16).cuda()
+    q = torch.randn(1, 64 * G, 128, generator=gen).to(torch.bfloat16).cuda()
+    pt = torch.tensor([[2, 0, 3, 1]], dtype=torch.int32).cuda()
+    sl = torch.tensor([4 * 16], dtype=torch.int32).cuda()
+    store = B.alloc_summaries(cfg, "cuda")
+    B.build_summaries(cfg, k, pt, sl, store)
+    want = B.score_pages(cfg, q, store, pt, sl, B.alloc_workspace(cfg, "cuda"))
+    n = heads // 64
+    big = B.Config(1, heads * G, heads, rank, 256, 4, 4)
+    assert heads * store.shape[-1] >= 1 << 24
+    got = B.score_pages(big, q.repeat(1, n, 1), store.repeat(1, n, 1), pt, sl,
+                        B.alloc_workspace(big, "cuda"))
+    torch.cuda.synchronize()
+    assert torch.isfinite(want).all()
+    torch.testing.assert_close(got.view(n, 64 * G, 4), want.expand(n, -1, -1), rtol=0, atol=1e-5)
+
+
 @pytest.mark.parametrize("G,rank,q", [(4, 8, "bf16"), (16, 8, "fp32"), (4, 2, "bf16")])
 def test_scores_with_an_unaligned_query(G, rank, q):
     """A query tensor that starts one element past a 16-byte boundary scores the same bits."""
