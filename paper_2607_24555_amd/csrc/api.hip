@@ -188,15 +188,27 @@ int dense_splits(const locks_cfg_t& c, int pps) {
   return (int)((((long)c.max_pages_per_seq << sub_page_log2(c)) + pps - 1) / pps);
 }
 
-// Blocks the workspace plan holds dense partials for, two per compute unit, and blocks
-// below which the launch of a batch halves the whole 256: with ragged lengths about half of
-// the grid is past its sequence's end, and four per compute unit balance the rest (8
-// sequences of 3K to 65K tokens, 8 KV heads: 237 us at 512 blocks, 214 at 1,024, 216 at
-// 2,048, 241 at 4,096, where the per-block latency shows).  One sequence is not ragged and
-// pays for the partials (1M, 2 KV heads: 61.4 us at the plan's split, 70.0 at half of it,
-// pages in the last-level cache), and smaller splits are as many blocks as they need (4 x
-// 16K, 8 KV heads: 13.6 us at 64 units a block, 14.6 at 32).
-constexpr long kDensePlanBlocks = 512, kDenseBlocks = 1024;
+// Blocks the workspace plan holds dense partials for: two per compute unit, as many as run
+// at once.
+constexpr long kDensePlanBlocks = 512;
+constexpr int kDenseMaxHalved = 96;  // splits a sequence that may be halved
+
+// Units per block of the launch: the plan's, but half of the whole 256 where the blocks
+// with tokens (no more than the grid, nor than the cache pool fills) come to between one
+// round of the chip and a quarter more, whose second round would be nearly empty, and the
+// partials stay few (the merge reads them one after the other).  Time at 128 units a block
+// against 256: 0.89 to 0.97 over 16 equal and ragged batches of 513 to 640 blocks and 3 to
+// 74 splits a sequence (two of 35: 1.00); 1.02 to 1.08 there from 118 splits on; past 640
+// blocks 0.96 to 1.12 (longest contexts worst), up to 512 1.00 to 1.11.
+int dense_launch_pages_per_split(const locks_cfg_t& c) {
+  const int pps = dense_pages_per_split(c, kDensePlanBlocks);
+  const long grid = (long)c.num_seqs * c.num_kv_heads * dense_splits(c, pps);
+  const long pool = ((long)c.num_blocks << sub_page_log2(c)) * c.num_kv_heads / kDensePagesPerSplit;
+  const long live = grid < pool ? grid : pool;
+  const bool half = c.num_seqs > 1 && pps == kDensePagesPerSplit && live > kDensePlanBlocks &&
+                    live <= kDensePlanBlocks * 5 / 4 && dense_splits(c, pps) <= kDenseMaxHalved;
+  return half ? pps / 2 : pps;
+}
 
 // The build for the configuration's page size: the register-resident kernel of
 // build.hip for 16-token pages (which also serves a step's overlapped build), the
@@ -396,10 +408,7 @@ int locks_dense_attend(const locks_cfg_t* cfg, const void* q, const void* k_cach
   // split always fits
   const WsPlan p = plan_workspace(*cfg);
   const size_t row = (size_t)cfg->num_seqs * cfg->num_q_heads * (kDim + 2) * sizeof(float);
-  int pps = dense_pages_per_split(*cfg, kDensePlanBlocks);
-  if (cfg->num_seqs > 1 && pps == kDensePagesPerSplit &&
-      (long)cfg->num_seqs * cfg->num_kv_heads * dense_splits(*cfg, pps) < kDenseBlocks)
-    pps /= 2;
+  int pps = dense_launch_pages_per_split(*cfg);
   while (pps < kDensePagesPerSplit && row * (size_t)dense_splits(*cfg, pps) > p.chk_pt_off) pps *= 2;
   return hip_status(launch_attend(*cfg, q, k_cache, v_cache, page_table, seq_lens, nullptr, pps,
                                   dense_splits(*cfg, pps), static_cast<float*>(ws), out, out_lse,

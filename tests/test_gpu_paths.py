@@ -502,8 +502,9 @@ def test_step_build_list_branches(name):
 
 @pytest.mark.parametrize("G,page", [(4, 16), (7, 16), (16, 64), (2, 32)])
 def test_dense_attention_of_ragged_batches(G, page):
-    """Dense attention where most blocks lie past their sequence's end: empty
-    sequences, single tokens, lengths on and around a wave's and a block's units."""
+    """Dense attention in blocks of eight units, two a wave, most of them past their
+    sequence's end: empty sequences, single tokens, lengths on and around a wave's and a
+    block's units."""
     lens = [16 * 64, 0, 1, 16 * 64 + 1, 16 * 16 - 1, 7000, 16 * 256, 16 * 3 + 9]
     spec = WorkloadSpec("dense", len(lens), 2 * G, 2, lens, 8, 16 * page, "bf16", "bf16",
                         page_size=page)
@@ -521,6 +522,52 @@ def test_dense_attention_of_ragged_batches(G, page):
                 continue
             assert max(rel_l2(got[g], o[g]) for g in range(G)) <= OUT_TOL
             np.testing.assert_allclose(lse[s, hs].double().cpu().numpy(), l, atol=LSE_TOL)
+
+
+@pytest.mark.parametrize("name,G,page,copies,pool,splits", [
+    ("half", 4, 16, 1, 16640, 10),          # 520 blocks, and a pool that can fill them
+    ("half", 2, 32, 1, 16640, 10),
+    ("whole, small pool", 1, 16, 1, 16000, 5),      # the pool fills 500 of the 520 at most
+    ("whole, large grid", 4, 16, 2, 16000, 5),      # 1,040 blocks
+    ("whole, no room", 16, 64, 1, 16640, 5),        # halved partials exceed the workspace
+])
+def test_dense_attention_splits_of_long_batches(name, G, page, copies, pool, splits):
+    """Dense attention whose blocks hold 256 units, and where its rule halves them, 128,
+    several of them a sequence (counted in the partials that the call leaves behind): empty
+    sequences, single tokens, lengths on and just past a wave's and a block's units, odd
+    counts of units.  pool: 16-token units per KV head in the cache."""
+    lens = [20480, 0, 1, 1024, 1025, 4096, 4097, 2048, 2049, 16 * 129, 16 * 385 + 5, 20479, 12345]
+    Hkv, sub = 8, page // 16
+    S, nb, mp = len(lens) * copies, pool // sub, 20480 // page
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    k, v = (torch.randn(nb, Hkv, page, 128, generator=gen, device="cuda", dtype=torch.bfloat16)
+            for _ in range(2))
+    q = torch.randn(len(lens), Hkv * G, 128, generator=gen, device="cuda").to(torch.bfloat16)
+    pt = torch.randperm(nb, generator=gen, device="cuda")[torch.arange(len(lens) * mp, device="cuda") % nb]
+    pt = pt.int().view(len(lens), mp)
+    sl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    cfg = B.Config(S, Hkv * G, Hkv, 8, 2 * page, mp, nb, page_size=page)
+    ws = B.alloc_workspace(cfg, "cuda")
+    ws.view(torch.int32).fill_(0x7fedcba9)            # a NaN that no partial is
+    out, lse = B.dense_attend(cfg, q.repeat(copies, 1, 1), k, v, pt.repeat(copies, 1), sl.repeat(copies), ws)
+    torch.cuda.synchronize()
+    written = torch.nonzero(ws.view(torch.int32) != 0x7fedcba9).max().item() + 1
+    assert written == S * Hkv * G * splits * 130, written / (S * Hkv * G * 130)
+    for c in range(1, copies):
+        assert torch.equal(out[c * len(lens):(c + 1) * len(lens)], out[:len(lens)])
+    for s, L in enumerate(lens):
+        if L == 0:
+            assert not out[s].any() and torch.isneginf(lse[s]).all()
+            continue
+        n = -(-L // page)
+        kd, vd = (x[pt[s, :n].long()].transpose(0, 1).reshape(Hkv, n * page, 128)[:, :L].double()
+                  for x in (k, v))
+        z = torch.matmul(q[s].double().view(Hkv, G, 128), kd.transpose(1, 2).contiguous()) / 128 ** 0.5
+        want_l = torch.logsumexp(z, -1).view(-1)
+        want = torch.matmul(torch.softmax(z, -1), vd).view(-1, 128)
+        err = (out[s].double() - want).norm(dim=-1) / want.norm(dim=-1)
+        assert err.max().item() <= OUT_TOL, (s, L, err.max().item())
+        assert (lse[s].double() - want_l).abs().max().item() <= LSE_TOL
 
 
 @pytest.mark.parametrize("G,copies", [(4, 1), (4, 86), (2, 86), (4, 172), (16, 172)])
