@@ -211,8 +211,8 @@ int dense_launch_pages_per_split(const locks_cfg_t& c) {
 }
 
 // The build for the configuration's page size: the register-resident kernel of
-// build.hip for 16-token pages (which also serves a step's overlapped build), the
-// LDS-resident one of build_page.hip for 32 and 64.
+// build.hip for 16-token pages (which also serves a step's overlapped build), that of
+// build_page.hip for 32 and 64.
 hipError_t build_pages(const locks_cfg_t& c, const void* k_cache, const int32_t* page_table,
                        const int32_t* seq_lens, const int32_t* build_list, int32_t n_items,
                        bool all_pages, void* summaries, float* mu, float* basis, float* coef,

@@ -562,9 +562,9 @@ void launch_typed(const locks_cfg_t& c, const void* q, const void* k_cache, cons
 }
 
 // bf16 MFMA kernel with the page count per wave fixed at compile time where the
-// list is split into 1, 2, 4 or 8 entries per wave.
+// list is split into 1, 2, 4 or 8 entries per wave (a selected table always is).
 template <bool kSelect>
-void launch_mfma(const locks_cfg_t& c, dim3 grid, hipStream_t st, const uint16_t* q,
+hipError_t launch_mfma(const locks_cfg_t& c, dim3 grid, hipStream_t st, const uint16_t* q,
                  const uint16_t* k_cache, const uint16_t* v_cache, const int32_t* page_table,
                  const int32_t* seq_lens, const int32_t* page_ids, int pages_per_split,
                  int n_splits, float* partial, float* out, float* out_lse, SelTable tb) {
@@ -587,8 +587,11 @@ void launch_mfma(const locks_cfg_t& c, dim3 grid, hipStream_t st, const uint16_t
     case 2: LOCKS_ATTEND_MFMA(2); break;
     case 4: LOCKS_ATTEND_MFMA(4); break;
     case 8: LOCKS_ATTEND_MFMA(8); break;
-    default: LOCKS_ATTEND_MFMA(0); break;
+    default:
+      if constexpr (kSelect) return hipErrorInvalidValue;
+      else { LOCKS_ATTEND_MFMA(0); }
   }
+  return hipGetLastError();
 #undef LOCKS_ATTEND_MFMA_N
 #undef LOCKS_ATTEND_MFMA
 }
@@ -600,11 +603,12 @@ hipError_t launch_attend(const locks_cfg_t& c, const void* q, const void* k_cach
                          const int32_t* page_ids, int pages_per_split, int n_splits,
                          float* partial, float* out, float* out_lse, hipStream_t st) {
   const bool qb = c.q_dtype == LOCKS_BF16, kb = c.kv_dtype == LOCKS_BF16;
+  hipError_t e = hipSuccess;
   if (qb && kb)
-    launch_mfma<false>(c, dim3(n_splits, c.num_kv_heads, c.num_seqs), st,
-                       static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k_cache),
-                       static_cast<const uint16_t*>(v_cache), page_table, seq_lens, page_ids,
-                       pages_per_split, n_splits, partial, out, out_lse, SelTable{});
+    e = launch_mfma<false>(c, dim3(n_splits, c.num_kv_heads, c.num_seqs), st,
+                           static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k_cache),
+                           static_cast<const uint16_t*>(v_cache), page_table, seq_lens, page_ids,
+                           pages_per_split, n_splits, partial, out, out_lse, SelTable{});
   else if (qb)
     launch_typed<uint16_t, float>(c, q, k_cache, v_cache, page_table, seq_lens, page_ids,
                                   pages_per_split, n_splits, partial, out, out_lse, st);
@@ -614,6 +618,7 @@ hipError_t launch_attend(const locks_cfg_t& c, const void* q, const void* k_cach
   else
     launch_typed<float, float>(c, q, k_cache, v_cache, page_table, seq_lens, page_ids,
                                pages_per_split, n_splits, partial, out, out_lse, st);
+  if (e != hipSuccess) return e;
   if (n_splits > 1)
     hipLaunchKernelGGL(merge_kernel, dim3(c.num_q_heads, c.num_seqs), dim3(kDim), 0, st,
                        c.num_q_heads, n_splits, partial, out, out_lse);
@@ -632,10 +637,11 @@ hipError_t launch_attend_select(const locks_cfg_t& c, const void* q, const void*
                                 float* out_lse, hipStream_t st) {
   const SelTable tb{sb, select_rows(c), select_width(c), select_chunk_pages(c), s_hat, lay, out_ids,
                     out_sel_lse};
-  launch_mfma<true>(c, dim3(n_splits, c.num_kv_heads, c.num_seqs), st,
-                    static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k_cache),
-                    static_cast<const uint16_t*>(v_cache), page_table, seq_lens, nullptr,
-                    pages_per_split, n_splits, partial, out, out_lse, tb);
+  const hipError_t e = launch_mfma<true>(
+      c, dim3(n_splits, c.num_kv_heads, c.num_seqs), st, static_cast<const uint16_t*>(q),
+      static_cast<const uint16_t*>(k_cache), static_cast<const uint16_t*>(v_cache), page_table,
+      seq_lens, nullptr, pages_per_split, n_splits, partial, out, out_lse, tb);
+  if (e != hipSuccess) return e;
   if (n_splits > 1)
     hipLaunchKernelGGL(merge_kernel, dim3(c.num_q_heads, c.num_seqs), dim3(kDim), 0, st,
                        c.num_q_heads, n_splits, partial, out, out_lse);

@@ -23,9 +23,10 @@
 //  * Back-transformation with kCPL components of one vector per lane: a reflector is one
 //    short dot product, a few lane exchanges and one update.
 // Bound: VALU issue (the Householder steps are about half of it) at four waves per SIMD
-// for 32 tokens and three for 64, which the registers of the inverse iteration and the
-// packed reflectors in LDS are held to.  2 x 128K tokens x 8 heads at r = 8: 748 us at 32
-// tokens and 1,526 at 64, where Gram rows in LDS, eigenvectors solved through LDS by r
+// for 32 tokens and three for 64 (ranks up to 8), which the packed reflectors in LDS and the
+// registers are held to: at 64 tokens by spilling 18 of them (fp32 keys 26; 76 and 108
+// bytes a lane), still faster than two waves without (1,526 us against 1,604).  2 x 128K
+// tokens x 8 heads at r = 8: 756 us at 32 tokens and 1,548 at 64, where Gram rows in LDS, eigenvectors solved through LDS by r
 // lanes and one reduction at a time took 1,470 and 3,900.
 #include "build_common.h"
 #include "locks_internal.h"

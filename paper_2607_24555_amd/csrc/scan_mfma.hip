@@ -313,8 +313,8 @@ __global__ __launch_bounds__(256) void scan_mfma_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Fast path for r in {2, 4, 8} and G in {4, 16} (G = 16 / NPACK); dispatched for
-// r in {2, 4} at G = 16 only (r = 8, and G = 4, have the kernels further below).
+// Fast path for r in {2, 4} at G = 16 (G = 16 / NPACK; the same ranks at G = 4, and r = 8,
+// have kernels of their own: scan_low.hip, scan_quad.h and scan_wide.h).
 //
 // Differences from the generic kernel above:
 //  * stage 1 runs on 16x16x64 int8 MFMA.  A basis nibble becomes an int8 with
@@ -554,7 +554,7 @@ hipError_t dispatch_scan(int r, int G, int basis, dim3 grid, hipStream_t st, int
                        max_pages, q, sum, pt, sl, s_hat, lay, part);               \
     return hipGetLastError();                                                               \
   }
-  // r = 2 and 4 at G = 16 (G = 4 took the low-rank kernel above)
+  // r = 2 and 4 at G = 16 (G = 4 took the low-rank kernel of scan_low.hip)
   LOCKS_SCAN_FAST(4, 1) LOCKS_SCAN_FAST(2, 1)
 #undef LOCKS_SCAN_FAST
 #define LOCKS_SCAN_MFMA_CASE(RR)                                                             \
@@ -565,9 +565,9 @@ hipError_t dispatch_scan(int r, int G, int basis, dim3 grid, hipStream_t st, int
   switch (r) {
     LOCKS_SCAN_MFMA_CASE(1) LOCKS_SCAN_MFMA_CASE(2) LOCKS_SCAN_MFMA_CASE(3)
     LOCKS_SCAN_MFMA_CASE(4) LOCKS_SCAN_MFMA_CASE(5) LOCKS_SCAN_MFMA_CASE(6)
-    LOCKS_SCAN_MFMA_CASE(7) LOCKS_SCAN_MFMA_CASE(8) LOCKS_SCAN_MFMA_CASE(9)
-    LOCKS_SCAN_MFMA_CASE(10) LOCKS_SCAN_MFMA_CASE(11) LOCKS_SCAN_MFMA_CASE(12)
-    LOCKS_SCAN_MFMA_CASE(13) LOCKS_SCAN_MFMA_CASE(14) LOCKS_SCAN_MFMA_CASE(15)
+    LOCKS_SCAN_MFMA_CASE(7) LOCKS_SCAN_MFMA_CASE(9) LOCKS_SCAN_MFMA_CASE(10)
+    LOCKS_SCAN_MFMA_CASE(11) LOCKS_SCAN_MFMA_CASE(12) LOCKS_SCAN_MFMA_CASE(13)
+    LOCKS_SCAN_MFMA_CASE(14) LOCKS_SCAN_MFMA_CASE(15)
     default:
       return hipErrorInvalidValue;
   }

@@ -329,7 +329,7 @@ hipError_t dispatch_scan_page(int r, int B, int wp, dim3 grid, hipStream_t st, i
     break;
   if (B != 32 && B != 64) return hipErrorInvalidValue;
   // four-head groups at the common ranks: four pages per stage-2 pass
-  if (H_q == 4 * H_kv && (r == 2 || r == 4 || r == 8)) {
+  if (H_q == 4 * H_kv && (r == 2 || r == 4)) {
 #define LOCKS_SCAN_PAGE4(RR)                                                                  \
     if (r == RR) {                                                                           \
       if (B == 32)                                                                           \
@@ -340,15 +340,15 @@ hipError_t dispatch_scan_page(int r, int B, int wp, dim3 grid, hipStream_t st, i
                            H_kv, max_pages, q, sum, pt, sl, s_hat, lay, part, wp);           \
       return hipGetLastError();                                                              \
     }
-    LOCKS_SCAN_PAGE4(2) LOCKS_SCAN_PAGE4(4) LOCKS_SCAN_PAGE4(8)
+    LOCKS_SCAN_PAGE4(2) LOCKS_SCAN_PAGE4(4)
 #undef LOCKS_SCAN_PAGE4
   }
   switch (r) {
     LOCKS_SCAN_PAGE_CASE(1) LOCKS_SCAN_PAGE_CASE(2) LOCKS_SCAN_PAGE_CASE(3)
     LOCKS_SCAN_PAGE_CASE(4) LOCKS_SCAN_PAGE_CASE(5) LOCKS_SCAN_PAGE_CASE(6)
-    LOCKS_SCAN_PAGE_CASE(7) LOCKS_SCAN_PAGE_CASE(8) LOCKS_SCAN_PAGE_CASE(9)
-    LOCKS_SCAN_PAGE_CASE(10) LOCKS_SCAN_PAGE_CASE(11) LOCKS_SCAN_PAGE_CASE(12)
-    LOCKS_SCAN_PAGE_CASE(13) LOCKS_SCAN_PAGE_CASE(14) LOCKS_SCAN_PAGE_CASE(15)
+    LOCKS_SCAN_PAGE_CASE(7) LOCKS_SCAN_PAGE_CASE(9) LOCKS_SCAN_PAGE_CASE(10)
+    LOCKS_SCAN_PAGE_CASE(11) LOCKS_SCAN_PAGE_CASE(12) LOCKS_SCAN_PAGE_CASE(13)
+    LOCKS_SCAN_PAGE_CASE(14) LOCKS_SCAN_PAGE_CASE(15)
     default:
       return hipErrorInvalidValue;
   }

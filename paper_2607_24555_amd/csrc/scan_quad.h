@@ -409,10 +409,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 4 && 
         blk_next = blk_after;
       }
     };
-    // with several steps a wave, the first step's records are on their way while the
-    // digits are formed (1M decode steps: 53.7 us, 55.3 the other way round); with one, in
-    // grids that leave most of the chip idle, holding those registers across the barrier
-    // costs more than it hides (32K decode steps: 26.2 us against 26.8)
+    // with one step a wave, in grids that leave most of the chip idle, holding the step's
+    // registers across the barrier costs more than it hides (32K decode steps: 26.2 us
+    // against 26.8); with several the first step's records are on their way while the
+    // digits are formed, as in the scan of 9 to 16 heads, where that was measured
     int blk0 = 0, blk1 = 0;
     if (n_steps == kSteps) {
       blk0 = lane_block_clamped<V>(pt_row, first, n_c, lane);

@@ -24,7 +24,7 @@
 // serves its V sub-pages, whose LSEs (lanes l ^ 16, l ^ 32) are merged at the end.
 //
 // Bound: the vector ALU and the latency of each step at two waves per SIMD (1M tokens,
-// two KV heads: one round of 2,048 waves).  30.4 us there; with stage 2 as a
+// two KV heads: one round of 2,048 waves, 251 registers).  30.4 us there; with stage 2 as a
 // block-diagonal 16x16x32 MFMA pair per 16 tokens (hi, lo) and per-quad row masks the
 // same layout took 31.6.
 #pragma once
@@ -317,9 +317,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
       }
     };
     // with several steps a wave, the first step's records are on their way while the
-    // digits are formed (1M decode steps: 53.7 us, 55.3 the other way round); with one, in
-    // grids that leave most of the chip idle, holding those registers across the barrier
-    // costs more than it hides (32K decode steps: 26.2 us against 26.8)
+    // digits are formed (1M decode steps: 53.7 us, 55.3 the other way round); with one, the
+    // digits come first, as in the scan of up to 8 heads, where that was measured
     int blk0 = 0, blk1 = 0;
     if (n_steps == kSteps) {
       blk0 = lane_block_clamped<V>(pt_row, first, n_c, lane);

@@ -95,7 +95,7 @@ def _attend_on_oracle_tables(d, refs):
 @pytest.mark.parametrize("q", ["bf16", "fp32"])
 @pytest.mark.parametrize("rank", list(range(1, 16)))
 def test_generic_scan_every_rank(rank, q):
-    """Two-head groups take the generic matrix-core scan at every rank."""
+    """Two-head groups: the generic matrix-core scan at every rank but 8, which has its own."""
     d = _dev("generic", 1, 2, 2, [16 * 130 + 5], rank, 256, q, q)
     store, recs = d.oracle_summaries()
     _, worst = _scores_against_oracle(d, store, recs)
