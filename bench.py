@@ -112,18 +112,20 @@ WORKLOADS = {
 # Each counter is divided by what it reads for the 1 GiB copy over 1 GiB, so the
 # result is in bytes.  Valid only for the scan sources these hashes name.
 SCAN_SOURCES = tuple("paper_2607_24555_amd/csrc/" + f for f in (
-    "scan.hip", "scan_quad.h", "scan_wide.h", "scan_low.hip", "scan_common.h", "locks_internal.h"))
+    "scan.hip", "scan_quad.h", "scan_quad_bf16.hip", "scan_quad_fp32.hip", "scan_wide.h",
+    "scan_low.hip", "scan_mfma.hip", "scan_page.hip", "scan_common.h", "scan_launch.h",
+    "locks_internal.h"))
 SCAN_TRAFFIC = {
     # workload: (sha256 of SCAN_SOURCES, FETCH_SIZE KiB, WRITE_SIZE KiB,
     #            copy FETCH factor, copy WRITE factor, profile file)
-    "1m": ("d72bd2acddea2be2", 55126.2, 8985.9, 0.500016, 1.0, "profiles/scan_1m_hbm_counters.md"),
-    "128k": ("d72bd2acddea2be2", 215269.2, 8618.9, 0.500016, 1.0, "profiles/scan_128k_hbm_counters.md"),
-    "128k-r2": ("d72bd2acddea2be2", 86822.1, 8668.3, 0.500014, 1.0, "profiles/scan_128k-r2_hbm_counters.md"),
-    "reasoning": ("d72bd2acddea2be2", 194797.6, 21323.1, 0.500014, 1.0, "profiles/scan_reasoning_hbm_counters.md"),
-    "1m-B32": ("d72bd2acddea2be2", 33145.2, 4518.8, 0.500014, 1.0, "profiles/scan_1m-B32_hbm_counters.md"),
-    "1m-B64": ("d72bd2acddea2be2", 21813.7, 2318.0, 0.500013, 1.0, "profiles/scan_1m-B64_hbm_counters.md"),
-    "128k-B32": ("d72bd2acddea2be2", 127531.1, 4382.0, 0.500015, 1.0, "profiles/scan_128k-B32_hbm_counters.md"),
-    "128k-B64": ("d72bd2acddea2be2", 84462.2, 2312.3, 0.500015, 1.0, "profiles/scan_128k-B64_hbm_counters.md"),
+    "1m": ("02a5d2ad56b25491", 56537.6, 8902.0, 0.500021, 1.0, "profiles/scan_1m_hbm_counters.md"),
+    "128k": ("02a5d2ad56b25491", 215534.5, 8778.7, 0.500019, 1.0, "profiles/scan_128k_hbm_counters.md"),
+    "128k-r2": ("02a5d2ad56b25491", 87079.3, 8715.4, 0.50002, 1.0, "profiles/scan_128k-r2_hbm_counters.md"),
+    "reasoning": ("02a5d2ad56b25491", 194866.4, 21573.7, 0.500019, 1.0, "profiles/scan_reasoning_hbm_counters.md"),
+    "128k-B32": ("02a5d2ad56b25491", 127742.9, 4614.8, 0.500019, 1.0, "profiles/scan_128k-B32_hbm_counters.md"),
+    "128k-B64": ("02a5d2ad56b25491", 84430.2, 2369.4, 0.500019, 1.0, "profiles/scan_128k-B64_hbm_counters.md"),
+    "1m-B32": ("02a5d2ad56b25491", 33193.7, 4432.3, 0.50002, 1.0, "profiles/scan_1m-B32_hbm_counters.md"),
+    "1m-B64": ("02a5d2ad56b25491", 21687.0, 2319.3, 0.50002, 1.0, "profiles/scan_1m-B64_hbm_counters.md"),
 }
 
 

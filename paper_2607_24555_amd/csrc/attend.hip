@@ -245,8 +245,8 @@ struct SelTable {
 // pages in flight (fully unrolled, so each wait covers one page); kPPW == 0: any
 // count up to 64, two units in flight, their addresses from one table read per wave
 // (dense attention of 8 ragged sequences, 1.1 GB of K and V: 272 us with a lookup per
-// unit and 64 stand-in loads in every block past its sequence's end, 214 us now, 5.2
-// TB/s, the rate of a plain copy).
+// unit and 64 stand-in loads in every block past its sequence's end, 214 us now: 5.2
+// TB/s, where a plain copy runs at 5.07).
 // kNK: survivors per lane of the selection merge (64 kNK per wave).
 // kOne: the list is one block's, which writes the output itself (the step of 64 sequences
 // x 8 KV heads, 16 entries each: 167.5 -> 161.5 us without the merge launch).  An instance

@@ -12,7 +12,7 @@ namespace locks {
 // size (larger pages as 16-token sub-pages): scan_quad for up to 8 heads a group,
 // scan_wide above.  Against the generic matrix-core scan that groups other than 4 and 16
 // heads took before: six ragged sequences of 20K to 256K tokens with eight-head groups
-// 114 -> 42 us; one head over 4K tokens 43 -> 7.5 us (one step per wave where the
+// 114 -> 46 us; one head over 4K tokens 43 -> 7.6 us (one step per wave where the
 // generic kernel walks 64 pages per wave).
 static bool use_quad_kernel(const locks_cfg_t& c) {
   return c.basis == LOCKS_BASIS_INT4 && c.rank == 8;

@@ -36,10 +36,10 @@
 //
 // Bound: at 16-token pages the scattered record gather (8 x 128K, four-head groups: 94 us,
 // 4.6 TB/s, where the gather alone runs at 5.2 to 5.7); at 32 and 64 tokens the vector
-// ALU's work per sub-page, so the per-step tail above is shared by the quads and the
-// instances for groups of four are held to 168 registers (three waves per SIMD; at two, 32-token
-// pages take 52 us for 46): 8 x 128K in 64-token pages 38.5 us.  The others' four-step
-// instances take 189 to 246 registers, two waves.
+// ALU's work per sub-page (58.5 and 44.5 us), so the per-step tail above is shared by the
+// quads and the instances for groups of four are held to 168 registers (three waves per
+// SIMD; at two, 32-token pages take 52 us for 46 with the store in the last-level cache).
+// The others' four-step instances take 189 to 246 registers, two waves.
 #pragma once
 
 #include "locks_internal.h"

@@ -24,7 +24,8 @@
 // serves its V sub-pages, whose LSEs (lanes l ^ 16, l ^ 32) are merged at the end.
 //
 // Bound: the vector ALU and the latency of each step at two waves per SIMD (1M tokens,
-// two KV heads: one round of 2,048 waves, 251 registers).  30.4 us there; with stage 2 as a
+// two KV heads: one round of 2,048 waves, 251 registers; with four query digits 256 and one
+// spilled).  30.4 us there; with stage 2 as a
 // block-diagonal 16x16x32 MFMA pair per 16 tokens (hi, lo) and per-quad row masks the
 // same layout took 31.6.
 #pragma once
