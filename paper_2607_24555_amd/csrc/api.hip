@@ -154,17 +154,26 @@ int check_ws(const locks_cfg_t* c, void* ws, size_t ws_bytes) {
 // grid would exceed ~512 blocks, so large batches stream several pages per
 // wave instead of paying per-block latency many times over.
 // (Counted in 16-token units: a table entry of B tokens is B / 16 of them.)
-// The vector-ALU kernel (fp32 queries or caches) takes a block per unit, doubled in the
-// same way, where the workspace holds that many partials: its blocks have one unit in
-// flight at a time.
+// The vector-ALU kernel (fp32 queries or caches) has one unit in flight at a time, so it
+// takes a block per unit, doubled while a list is more than 64 splits (the merge reads 32 in
+// a round trip) or more than the workspace holds, and while the grid exceeds 1,024 blocks
+// (four per compute unit run at once), the blocks of a group's further heads counted.  With
+// neither count, one sequence and KV head, 10 heads, 256 units: 25.2 us in 256 splits, 14.3
+// in 64; two sequences and KV heads, 16 heads, 256 units: 29.1 us in 1,024 blocks a head
+// block, 19.7 in 256 (both lost to the kernel before, 20.0 and 23.5).
 int sparse_pages_per_split(const locks_cfg_t& c, int plan_splits) {
   const long units = (long)c.num_seqs * c.num_kv_heads;
-  const int k = page_budget(c) << sub_page_log2(c);
-  int pps = kSparsePagesPerSplit;
+  const int k = page_budget(c) << sub_page_log2(c);  // units of a table
   if (c.q_dtype != LOCKS_BF16 || c.kv_dtype != LOCKS_BF16) {
-    pps = 1;
-    while (pps < kSparsePagesPerSplit && (k + pps - 1) / pps > plan_splits) pps *= 2;
+    const int head_blocks = (c.num_q_heads / c.num_kv_heads + 3) / 4;
+    const int most = plan_splits < 64 ? plan_splits : 64;
+    int pps = 1;
+    while (pps < kSparsePagesPerSplit && (k + pps - 1) / pps > most) pps *= 2;
+    while (pps < 32 && units * (head_blocks > 2 ? head_blocks : 2) * ((k + pps - 1) / pps) > 1024)
+      pps *= 2;
+    return pps;
   }
+  int pps = kSparsePagesPerSplit;
   while (pps < 32 && units * ((k + pps - 1) / pps) > 512) pps *= 2;
   return pps;
 }

@@ -524,6 +524,48 @@ def test_dense_attention_of_ragged_batches(G, page):
             np.testing.assert_allclose(lse[s, hs].double().cpu().numpy(), l, atol=LSE_TOL)
 
 
+@pytest.mark.parametrize("S,Hkv,G,budget,page,q,splits", [
+    (1, 1, 1, 256, 16, "fp32", 16),       # a unit a block
+    (1, 1, 7, 4096, 32, "bf16", 64),      # 256 units: at most 64 splits
+    (2, 2, 16, 4096, 16, "bf16", 64),     # 1,024 blocks with the heads' further blocks
+    (4, 2, 16, 2048, 16, "fp32", 32),     # 128 units, 2,048 blocks in 64 splits
+    (4, 2, 3, 2048, 64, "bf16", 64),
+])
+def test_fp32_sparse_attention_splits(S, Hkv, G, budget, page, q, splits):
+    """Sparse attention over fp32 caches: the splits that its rule takes (counted in the
+    partials that the call leaves behind), and its output over given tables, one of them
+    padded and one with a partial last page, against 64 bits."""
+    k = budget // page
+    n = max(64, 2 * k)
+    gen = torch.Generator(device="cuda").manual_seed(13)
+    kc, vc = (torch.randn(S * n, Hkv, page, 128, generator=gen, device="cuda") for _ in range(2))
+    qq = torch.randn(S, Hkv * G, 128, generator=gen, device="cuda").to(torch.bfloat16 if q == "bf16" else torch.float32)
+    pt = torch.randperm(S * n, generator=gen, device="cuda").int().view(S, n)
+    sl = torch.full((S,), n * page - 5, dtype=torch.int32, device="cuda")
+    ids = torch.stack([torch.randperm(n - 1, generator=gen, device="cuda")[:k].sort()[0]
+                       for _ in range(S * Hkv)]).int().view(S, Hkv, k)
+    ids[..., -1] = n - 1
+    ids[-1, -1, -3:] = -1
+    cfg = B.Config(S, Hkv * G, Hkv, 8, budget, n, S * n, B.LOCKS_FP32, DT[q], page_size=page)
+    ws = B.alloc_workspace(cfg, "cuda")
+    ws.view(torch.int32).fill_(0x7fedcba9)            # a NaN that no partial is
+    out, lse = B.sparse_attend(cfg, qq, kc, vc, pt, sl, ids, ws)
+    torch.cuda.synchronize()
+    written = (ws.view(torch.int32) != 0x7fedcba9).sum().item()
+    assert written == S * Hkv * G * splits * 130, written / (S * Hkv * G * 130)
+    for s in range(S):
+        for h in range(Hkv):
+            mine = ids[s, h][ids[s, h] >= 0].long()
+            kd, vd = (x[pt[s, mine].long(), h].reshape(-1, 128).double() for x in (kc, vc))
+            live = (mine[:, None] * page + torch.arange(page, device="cuda")).view(-1) < sl[s]
+            z = torch.matmul(qq[s, h * G:(h + 1) * G].double(), kd.t().contiguous()) / 128 ** 0.5
+            z = z.masked_fill(~live, -float("inf"))
+            want = torch.matmul(torch.softmax(z, -1), vd)
+            got = out[s, h * G:(h + 1) * G].double()
+            assert ((got - want).norm(dim=-1) / want.norm(dim=-1)).max().item() <= 1e-5
+            assert (lse[s, h * G:(h + 1) * G].double() - torch.logsumexp(z, -1)).abs().max().item() <= 1e-5
+
+
 @pytest.mark.parametrize("name,G,page,copies,pool,splits", [
     ("half", 4, 16, 1, 16640, 10),          # 520 blocks, and a pool that can fill them
     ("half", 2, 32, 1, 16640, 10),
